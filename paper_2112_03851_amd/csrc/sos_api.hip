@@ -140,7 +140,7 @@ struct sos_ctx {
   double* team_part = nullptr;   // team partial sums
   bool tuned = false;    // fused block shape chosen (explicit or autotuned)
   double tune_ms = 0.0;  // duration of the chosen shape in the tuning run
-  size_t lds_limit = 0;
+  size_t lds_limit = 0;  // LDS of a workgroup, static and dynamic together
   // graph of (check_every outer iterations + check)
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
@@ -282,7 +282,8 @@ int build_seg(sos_ctx* c) {
     }
     g.bfirst.push_back((int32_t)g.blocks.size());
   }
-  if (lds64 > c->lds_limit) return fail(SOS_EINVAL, "subdomain plane needs %zu bytes of LDS (limit %zu)", lds64, c->lds_limit);
+  if (lds64 + kMarchStatic > c->lds_limit)
+    return fail(SOS_EINVAL, "subdomain plane needs %zu bytes of LDS (limit %zu)", lds64 + kMarchStatic, c->lds_limit);
   g.L.nblocks = (int32_t)g.blocks.size();
   g.L.threads = threads;
   g.L.cpt = cpt;
@@ -322,7 +323,8 @@ int fused_shape(sos_ctx* c, int threads, int cpt = 0, int ra = 0, int res = 0) {
     return fail(SOS_EINVAL, "block of %d threads with %d columns each exceeds the kernel bound %d", threads, cpt,
                 launch_bound(cpt));
   const size_t lds = fused_lds_need(c, threads, cpt);
-  if (lds > c->lds_limit) return fail(SOS_EINVAL, "fused kernel needs %zu bytes of LDS (limit %zu)", lds, c->lds_limit);
+  if (lds + kFusedStatic > c->lds_limit)
+    return fail(SOS_EINVAL, "fused kernel needs %zu bytes of LDS (limit %zu)", lds + kFusedStatic, c->lds_limit);
   if (ra) {
     if (threads % 64) return fail(SOS_EINVAL, "wave-owned rows need a multiple of 64 threads");
     for (auto& s : c->subs) {
@@ -452,7 +454,7 @@ std::vector<Shape> fused_candidates(const sos_ctx* c) {
   const int smax = smax_plane(c);
   std::vector<Shape> out;
   auto add = [&](Shape sh) {
-    if (sh.threads > launch_bound(sh.cpt) || fused_lds_need(c, sh.threads, sh.cpt) > c->lds_limit) return;
+    if (sh.threads > launch_bound(sh.cpt) || fused_lds_need(c, sh.threads, sh.cpt) + kFusedStatic > c->lds_limit) return;
     if (std::find(out.begin(), out.end(), sh) == out.end()) out.push_back(sh);
   };
   for (int cpt = 1; cpt <= 4; ++cpt) {
@@ -732,7 +734,7 @@ FusedArgs fused_args(sos_ctx* c) {
   if (c->fused_res && c->fp32 && a.zu) {
     for (int words = 2; words >= 1 && !a.res; --words) {
       const size_t total = std::max(fused_res_lds(c, words), c->fused_lds);
-      if (total <= c->lds_limit) {
+      if (total + kFusedStatic <= c->lds_limit) {
         a.res = words == 2 ? 1 : 2;
         a.lds_bytes = (uint32_t)total;
       }
@@ -1753,7 +1755,7 @@ int sos_apply_local(sos_ctx* c, int32_t precision, const void* x, void* y) {
   if (!c || !x || !y) return fail(SOS_EINVAL, "NULL argument");
   if (precision != SOS_FP64 && precision != SOS_FP32_INNER) return fail(SOS_EINVAL, "precision invalid");
   SegLaunch L = c->seg.L;
-  if (precision == SOS_FP32_INNER && L.lds32 > c->lds_limit) return fail(SOS_EINVAL, "LDS limit");
+  if (precision == SOS_FP32_INNER && L.lds32 + kMarchStatic > c->lds_limit) return fail(SOS_EINVAL, "LDS limit");
   HIPCHK(launch_apply(c->dev, L, precision == SOS_FP32_INNER, x, y, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return SOS_OK;

@@ -1,0 +1,83 @@
+// Launches of the on-chip fused CG kernel (sos_chip.h) for one set of
+// variants, SOS_CHIP_SET (compiled once per value), and their dispatch
+// (SOS_CHIP_SET 0).
+#include "sos_chip.h"
+
+#ifndef SOS_CHIP_SET
+#error SOS_CHIP_SET must be defined (0..5)
+#endif
+
+namespace sos {
+
+template <int SET>
+hipError_t launch_chip_set(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
+                           int* per_cu);
+
+template <typename T, int P, int NP, bool Q, bool WL>
+static hipError_t chip_one(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
+                           int* per_cu) {
+  if (per_cu)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void*)k_chip_cg<T, P, NP, Q, WL>, threads,
+                                                        a.lds_bytes);
+  hipLaunchKernelGGL((k_chip_cg<T, P, NP, Q, WL>), dim3(a.n_teams * a.team), dim3(threads), a.lds_bytes, st, d,
+                     L.bfirst, a);
+  return hipGetLastError();
+}
+
+template <typename T, int P, bool WL>
+static hipError_t chip_np(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
+                          int* per_cu) {
+  if (a.chip_planes != P || (a.chip_wl != 0) != WL) return hipErrorInvalidValue;
+  if (a.chip_pairs == 17)
+    return d.hasq ? chip_one<T, P, 17, true, WL>(d, L, threads, a, st, per_cu)
+                  : chip_one<T, P, 17, false, WL>(d, L, threads, a, st, per_cu);
+  if (a.chip_pairs == 0)
+    return d.hasq ? chip_one<T, P, 0, true, WL>(d, L, threads, a, st, per_cu)
+                  : chip_one<T, P, 0, false, WL>(d, L, threads, a, st, per_cu);
+  return hipErrorInvalidValue;
+}
+
+template <>
+hipError_t launch_chip_set<SOS_CHIP_SET>(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a,
+                                         hipStream_t st, int* per_cu) {
+#if SOS_CHIP_SET == 0
+  return chip_np<float, 17, false>(d, L, threads, a, st, per_cu);
+#elif SOS_CHIP_SET == 1
+  return chip_np<float, 17, true>(d, L, threads, a, st, per_cu);
+#elif SOS_CHIP_SET == 2
+  return chip_np<float, 9, true>(d, L, threads, a, st, per_cu);
+#elif SOS_CHIP_SET == 5
+  return chip_np<float, 12, true>(d, L, threads, a, st, per_cu);
+#elif SOS_CHIP_SET == 3
+  return chip_np<float, 5, true>(d, L, threads, a, st, per_cu);
+#else
+  return chip_np<double, 5, true>(d, L, threads, a, st, per_cu);
+#endif
+}
+
+#if SOS_CHIP_SET == 0
+template <>
+hipError_t launch_chip_set<1>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
+template <>
+hipError_t launch_chip_set<2>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
+template <>
+hipError_t launch_chip_set<3>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
+template <>
+hipError_t launch_chip_set<5>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
+template <>
+hipError_t launch_chip_set<4>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
+
+hipError_t launch_chip(const Dev& d, const SegLaunch& L, int fp32, int threads, const FusedArgs& a, hipStream_t st,
+                       int* per_cu) {
+  if (threads > kChipThreads || a.team < 1 || a.n_teams < (per_cu ? 0 : 1)) return hipErrorInvalidValue;
+  if (!fp32) return launch_chip_set<4>(d, L, threads, a, st, per_cu);
+  if (a.chip_planes == 17)
+    return a.chip_wl ? launch_chip_set<1>(d, L, threads, a, st, per_cu)
+                     : launch_chip_set<0>(d, L, threads, a, st, per_cu);
+  if (a.chip_planes == 12) return launch_chip_set<5>(d, L, threads, a, st, per_cu);
+  return a.chip_planes == 9 ? launch_chip_set<2>(d, L, threads, a, st, per_cu)
+                            : launch_chip_set<3>(d, L, threads, a, st, per_cu);
+}
+#endif
+
+}  // namespace sos

@@ -65,6 +65,11 @@ __host__ __device__ inline size_t march_lds_bytes(int nx, int ny, int zlen, int 
   return kPlanes * sp * (size_t)march_segments(nx, ny, zlen, threads, cpt) * elem;
 }
 
+// Static LDS bytes of the march kernels (block sums) and of the fused kernel
+// (its sums and its team's): part of the same 160 KB as the dynamic LDS. A
+// launch beyond them is not refused, it aborts the queue.
+constexpr size_t kMarchStatic = 384, kFusedStatic = 1120;
+
 // f_s from a per-element density (FP64), for all subdomains.
 hipError_t launch_load_density(const Dev& d, int max_n, const double* drho, double G,
                                double* f_loc, hipStream_t st);

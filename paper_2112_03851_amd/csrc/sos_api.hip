@@ -1074,6 +1074,7 @@ int autotune(sos_ctx* c) {
     *out = INFINITY;
     int rc = ensure_fmap(c);
     if (rc) return rc;
+    HIPCHK(hipMemsetAsync(c->flags, 0, sizeof(int32_t), st));
     for (int rep = 0; rep < 3; ++rep) {
       HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
       HIPCHK(launch_residual(c->dev, c->seg.L, c->fp32, false, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part,
@@ -1091,6 +1092,10 @@ int autotune(sos_ctx* c) {
       HIPCHK(hipEventElapsedTime(&ms, e0, e1));
       *out = std::min(*out, (double)ms);
     }
+    // a launch that breaks down ends early and would win
+    int32_t broken = 0;
+    HIPCHK(hipMemcpy(&broken, c->flags, sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (broken) *out = INFINITY;
     return SOS_OK;
   };
   double best = INFINITY;
@@ -1141,7 +1146,9 @@ int autotune(sos_ctx* c) {
   if (rc) return rc;
   c->tune_ms = best;
   invalidate_graph(c);
-  if (!partial) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best);
+  // every candidate broke down (a load that is not finite): nothing was learned
+  if (!std::isfinite(best)) c->tuned = false;
+  else if (!partial) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best);
   return SOS_OK;
 }
 

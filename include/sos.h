@@ -132,7 +132,9 @@ typedef struct {
                           direction p and the correction x (or x alone) in
                           LDS for the whole launch where they fit (uniform
                           z-ranges; with block != 0 it does, the autotuner
-                          tries both); 0: never                             */
+                          tries both), and with block 0 the autotuner may
+                          take, in either precision, the form that keeps the
+                          whole state of an inner solve on the chip; 0: never */
   int32_t march;       /* axis every subdomain is marched along (set up once):
                           0 (default) z, or for a subdomain whose x-y node
                           plane exceeds 4096 nodes the axis across its
@@ -169,7 +171,9 @@ typedef struct {
   int32_t wave_rows;      /* 1: each wave of the fused CG kernel owns whole
                              x-rows of the plane (one barrier per plane)       */
   int32_t resident;       /* the fused CG kernel keeps in LDS: 1 p and x,
-                             2 x alone (p and x do not fit), 0 neither         */
+                             2 x alone (p and x do not fit), 0 neither; 3: the
+                             whole state stays on the chip (a thread owns a
+                             pair of x-neighbours, cols_per_thread 2)          */
 } sos_stats;
 
 /* Fill *opts with defaults for the given precision. */

@@ -1,7 +1,8 @@
 """Build the HIP library libsos.so in-tree for gfx950 with hipcc.
 
 The sources compile to objects in parallel (the fused CG kernel once per
-number of x-y columns per thread, 1 to 4) and are linked into one shared
+number of x-y columns per thread, 1 to 4, its on-chip form once per set of
+variants) and are linked into one shared
 library next to this file.
 """
 from __future__ import annotations
@@ -22,7 +23,8 @@ ARCH = "gfx950"
 UNITS = [("sos_kernels.hip", [], "sos_kernels.o"),
          ("sos_api.hip", [], "sos_api.o"),
          ("sos_cmaes.cpp", [], "sos_cmaes.o")] + \
-        [("sos_fused.hip", [f"-DSOS_FUSED_CPT={c}"], f"sos_fused_c{c}.o") for c in (1, 2, 3, 4)]
+        [("sos_fused.hip", [f"-DSOS_FUSED_CPT={c}"], f"sos_fused_c{c}.o") for c in (1, 2, 3, 4)] + \
+        [("sos_chip.hip", [f"-DSOS_CHIP_SET={k}"], f"sos_chip_{k}.o") for k in (0, 1, 2, 3, 4, 5)]
 
 
 def hipcc():

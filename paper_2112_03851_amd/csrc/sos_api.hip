@@ -83,6 +83,14 @@ int scratch_address(void** out) {
 
 }  // namespace
 
+// Launch of the on-chip fused kernel (sos_chip.h).
+struct ChipPlan {
+  int planes = 0, pairs = 0, wl = 0;  // kernel variant
+  int threads = 0, slots = 0;         // block size, most pairs of a plane
+  int team = 0, n_teams = 0;          // blocks per subdomain, teams of the grid
+  size_t lds = 0, w = 0, x = 0, halo = 0, mail = 0;  // dynamic LDS, workspace bytes
+};
+
 struct sos_ctx {
   sos_mesh mesh{};
   sos_opts opts{};
@@ -135,7 +143,12 @@ struct sos_ctx {
   // fused kernel launch shape
   int fused_threads = 0, fused_cpt = 1, fused_team = 1;
   int fused_ra = 0;   // wave-owned rows in the fused kernel
-  int fused_res = 0;  // p and x resident in LDS when they fit (FP32, uniform z)
+  int fused_res = 0;  // 1: p and x resident in LDS when they fit (FP32, uniform z); 3: on-chip form
+  // on-chip form: the launch for the current teams, and its workspaces
+  ChipPlan chip{};
+  void* chip_ws = nullptr;
+  size_t chip_bytes = 0;
+  int32_t* queue = nullptr;  // ticket and job counters
   size_t fused_lds = 0;
   double* team_part = nullptr;   // team partial sums
   bool tuned = false;    // fused block shape chosen (explicit or autotuned)
@@ -175,7 +188,7 @@ void release(sos_ctx* c) {
   void* ptrs[] = {c->d_subs, c->d_faces, c->d_expairs, c->d_fmap, c->seg.d_blocks, c->seg.d_bfirst, c->u, c->f, c->b,
                   c->fxf, c->bxf,
                   c->lam, c->ut, c->rho, c->r, c->x, c->p0, c->p1, c->q, c->r1, c->w1, c->s0, c->s1,
-                  c->part, c->part_norm, c->d_res, c->psi, c->team_part,
+                  c->part, c->part_norm, c->d_res, c->psi, c->team_part, c->chip_ws, c->queue,
                   c->scal, c->ndone, c->counters, c->flags};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -308,6 +321,7 @@ size_t fused_lds_need(const sos_ctx* c, int threads, int cpt) {
 // Sets the fused kernel's block shape; cpt = 0 picks the fewest columns per
 // thread that cover the largest x-y plane.
 int fused_shape(sos_ctx* c, int threads, int cpt = 0, int ra = 0, int res = 0) {
+  if (c->fused_res == 3) c->fmap_dirty = true;  // the block table of the on-chip form is another
   const int smax = smax_plane(c);
   if (threads == 0) {
     int k = 1;
@@ -340,6 +354,14 @@ int fused_shape(sos_ctx* c, int threads, int cpt = 0, int ra = 0, int res = 0) {
   c->fused_res = res ? 1 : 0;
   c->fused_lds = lds;
   return SOS_OK;
+}
+
+// The on-chip form (its launch follows from the team size, chip_plan).
+void chip_shape(sos_ctx* c) {
+  c->fused_cpt = 2;  // a thread's columns: one pair of x-neighbours
+  c->fused_ra = 1;
+  c->fused_res = 3;
+  c->fmap_dirty = true;
 }
 
 // True when every block of the fused kernel (every subdomain and team member)
@@ -406,6 +428,73 @@ void make_buckets(sos_ctx* c) {
   }
 }
 
+int dalloc_v(void** p, size_t bytes);
+
+// Launch of the on-chip form for one team size over all subdomains: false
+// where it does not apply. The smallest number of planes per block that a
+// kernel variant holds; w in LDS where it fits beside p and x; as many teams
+// as the GPU holds at once.
+bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
+  if (!c->opts.resident) return false;
+  const size_t es = c->fp32 ? 4 : 8;
+  ChipPlan p;
+  p.team = team;
+  // the kernel variant for 17 pairs a row (16 elements; a row that ends before
+  // its last mid-point has 16 and an idle pair), else any number
+  int most = 0, least = INT32_MAX;
+  for (const SubDesc& d : c->subs) {
+    const int np = chip_pairs(d.n[0], d.klo[0]);
+    most = std::max(most, np);
+    least = std::min(least, np);
+  }
+  p.pairs = most == 17 && least >= 16 ? 17 : 0;
+  auto pairs_of = [&](const SubDesc& d) { return p.pairs ? p.pairs : chip_pairs(d.n[0], d.klo[0]); };
+  int waves = 1, zmax = 0;
+  for (const SubDesc& d : c->subs) {
+    const int np = pairs_of(d), R = chip_rows(np);
+    if (R < 1 || (team > 1 && d.n[2] < 2 * team)) return false;
+    waves = std::max(waves, (d.n[1] + R - 1) / R);
+    zmax = std::max(zmax, (d.n[2] + team - 1) / team);
+    p.slots = std::max(p.slots, np * d.n[1]);
+  }
+  p.threads = 64 * (waves + 1);  // one more wave for the sums
+  if (p.threads > kChipThreads) return false;
+  auto lds_of = [&](bool wl) {
+    size_t b = 0;
+    for (const SubDesc& d : c->subs)
+      b = std::max(b, chip_lds(pairs_of(d), d.n[1], (d.n[2] + team - 1) / team, es, wl));
+    return b;
+  };
+  const size_t limit = c->lds_limit - kChipStatic;
+  p.wl = lds_of(true) <= limit;
+  p.lds = lds_of(p.wl);
+  if (p.lds > limit) return false;
+  p.planes = zmax <= 5 ? 5 : (zmax <= 9 ? 9 : (zmax <= 12 ? 12 : 17));
+  if (zmax > p.planes || (!c->fp32 && p.planes > 5) || (p.planes < 17 && !p.wl)) return false;
+  FusedArgs a = {};
+  a.team = team;
+  a.chip_planes = p.planes;
+  a.chip_pairs = p.pairs;
+  a.chip_wl = p.wl;
+  a.lds_bytes = (uint32_t)p.lds;
+  int dev = 0, cus = 0, per_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      launch_chip(c->dev, c->seg.L, c->fp32, p.threads, a, c->stream, &per_cu) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  p.n_teams = std::min((int)c->subs.size(), per_cu * cus / team);
+  if (p.n_teams < 1) return false;
+  const size_t blocks = (size_t)p.n_teams * team;
+  p.w = p.wl ? 0 : blocks * (p.planes + kChipAhead) * p.threads * 2 * es;
+  p.x = p.planes > 12 ? blocks * (p.planes + kChipAhead) * p.threads * 2 * es : 0;
+  p.halo = blocks * kChipPrivate * p.threads * 4 * es;
+  p.mail = team > 1 ? blocks * 8 * (size_t)p.slots * 4 * es : 0;
+  *out = p;
+  return true;
+}
+
 // The fused kernel's block table: teams in the order of c->order (largest
 // subdomain first). With a team of two or more blocks anywhere, the members of
 // every team share blockIdx % 8 (one XCD under round-robin dispatch, so their
@@ -416,7 +505,24 @@ int ensure_fmap(sos_ctx* c) {
   if (!c->fmap_dirty) return SOS_OK;
   std::vector<TeamSlot>& m = c->fmap;
   m.clear();
-  if (c->fused_team <= 1) {
+  const bool chip = c->fused_res == 3;
+  if (chip) {
+    // one entry per subdomain: the order in which the teams take them
+    if (!chip_plan(c, c->fused_team, &c->chip)) return fail(SOS_EINVAL, "the on-chip fused kernel does not fit team %d", c->fused_team);
+    c->fused_threads = c->chip.threads;
+    const size_t need = c->chip.w + c->chip.x + c->chip.halo + c->chip.mail;
+    if (need > c->chip_bytes) {
+      HIPCHK(hipStreamSynchronize(c->stream));
+      if (c->chip_ws) (void)hipFree(c->chip_ws);
+      c->chip_ws = nullptr;
+      c->chip_bytes = 0;
+      if (int rc = dalloc_v(&c->chip_ws, need)) return rc;
+      // no word of the mailboxes carries a sequence number yet
+      HIPCHK(hipMemsetAsync(c->chip_ws, 0, need, c->stream));
+      c->chip_bytes = need;
+    }
+  }
+  if (chip || c->fused_team <= 1) {
     for (int32_t s : c->order) m.push_back({s, 0, 1, 0});
   } else {
     std::vector<std::vector<TeamSlot>> q(8);
@@ -475,6 +581,8 @@ std::vector<Shape> fused_candidates(const sos_ctx* c) {
     for (size_t i = 0; i < n; ++i) out.push_back({out[i].threads, out[i].cpt, out[i].ra, 1});
   }
   // (shapes with res = 1 keep p and x in LDS, or x alone where both do not fit)
+  // the on-chip form; it comes first: a near-equal other shape does not replace it
+  if (c->opts.resident) out.insert(out.begin(), Shape{0, 2, 1, 3});
   return out;
 }
 
@@ -507,7 +615,7 @@ std::string tune_key(const sos_ctx* c) {
     for (int a = 0; a < 3; ++a) mix((uint64_t)s.n[a]);
   mix((uint64_t)c->subs.size());
   char buf[160];
-  snprintf(buf, sizeof buf, "gfx950|v3|%s|%016llx|tol%.3g|abs%.3g|max%d", c->fp32 ? "fp32" : "fp64",
+  snprintf(buf, sizeof buf, "gfx950|v4|%s|%016llx|tol%.3g|abs%.3g|max%d", c->fp32 ? "fp32" : "fp64",
            (unsigned long long)h, c->opts.inner_tol, c->opts.inner_abs, c->opts.max_inner);
   return buf;
 }
@@ -702,7 +810,7 @@ int check_passes(sos_ctx* c, double* ut, double* rho, double* part, double* dres
 int enqueue_check(sos_ctx* c, double* phi) { return check_passes(c, c->ut, c->rho, c->part_norm, c->d_res, phi); }
 
 FusedArgs fused_args(sos_ctx* c) {
-  FusedArgs a;
+  FusedArgs a = {};
   a.fmap = c->d_fmap;
   a.nblocks = (int32_t)c->fmap.size();
   a.res_part = c->part;
@@ -723,6 +831,31 @@ FusedArgs fused_args(sos_ctx* c) {
   a.iters_total = c->counters;
   a.team = c->fused_team;
   a.team_part = c->team_part;
+  a.queue = c->queue;
+  a.n_jobs = (int32_t)c->subs.size();
+  a.n_teams = 0;
+  if (c->fused_res == 3) {
+    const ChipPlan& p = c->chip;
+    a.flags = c->flags;
+    a.spin_ticks = c->spin_ticks;
+    a.tag_skew = c->tag_skew;
+    a.zu = 1;
+    a.rows = 1;
+    a.res = 3;
+    a.lds_bytes = (uint32_t)p.lds;
+    a.n_teams = p.n_teams;
+    a.nblocks = p.n_teams * p.team;
+    a.chip_planes = p.planes;
+    a.chip_pairs = p.pairs;
+    a.chip_wl = p.wl;
+    a.chip_slots = p.slots;
+    char* ws = static_cast<char*>(c->chip_ws);
+    a.chip_w = ws;
+    a.chip_x = ws + p.w;
+    a.chip_halo = ws + p.w + p.x;
+    a.chip_mail = ws + p.w + p.x + p.halo;
+    return a;
+  }
   a.zu = fused_one_segment(c) ? 1 : 0;
   a.rows = c->fused_ra;
   // resident p and x where they fit, else x alone, else neither
@@ -753,14 +886,20 @@ hipError_t copy_load_to_rhs(sos_ctx* c) {
 // One outer iteration in the batched form; ev (optional) brackets the fused kernel.
 // With one block per subdomain, the fused kernel's next launch takes the
 // subdomains in decreasing order of the work of their last inner solve.
+// In the on-chip form, where a team takes several subdomains, in the order in
+// which the teams take them.
 bool schedule_by_work(const sos_ctx* c) {
+  if (c->fused_res == 3) return c->opts.schedule && c->chip.n_teams < (int)c->subs.size();
   return c->opts.schedule && c->fused_team <= 1 && c->fmap.size() == c->subs.size();
 }
+
+// The counters of the on-chip form, which the residual kernel clears (else null).
+int32_t* queue_of(sos_ctx* c) { return c->fused_res == 3 ? c->queue : nullptr; }
 
 int enqueue_batched_iteration(sos_ctx* c, hipEvent_t ev0, hipEvent_t ev1) {
   hipStream_t st = c->stream;
   HIPCHK(launch_residual(c->dev, c->seg.L, c->fp32, false, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part,
-                         c->fused_team > 1 ? c->team_part : nullptr, st));
+                         c->fused_team > 1 ? c->team_part : nullptr, queue_of(c), st));
   if (ev0) HIPCHK(hipEventRecord(ev0, st));
   HIPCHK(launch_fused_cg(c->dev, c->seg.L, c->fp32, c->fused_threads, c->fused_cpt, c->fused_lds, fused_args(c), st));
   if (ev1) HIPCHK(hipEventRecord(ev1, st));
@@ -776,7 +915,7 @@ int enqueue_batched_iteration(sos_ctx* c, hipEvent_t ev0, hipEvent_t ev1) {
 int stepwise_iteration(sos_ctx* c) {
   hipStream_t st = c->stream;
   const SegLaunch& L = c->seg.L;
-  HIPCHK(launch_residual(c->dev, L, c->fp32, true, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part, nullptr, st));
+  HIPCHK(launch_residual(c->dev, L, c->fp32, true, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part, nullptr, nullptr, st));
   HIPCHK(launch_cg_init(c->dev, L, c->part, c->opts.inner_tol, c->opts.inner_abs, c->scal, c->ndone, st));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->opts.timing) {
@@ -1044,9 +1183,18 @@ int autotune(sos_ctx* c) {
   const bool partial = c->opts.block != 0 || c->opts.team != 0;
   int th = 0, cp = 0, ra = 0, res = 0;
   std::vector<int32_t> bt;
-  if (!partial && tune_lookup(key, &th, &cp, &bt, &ra, &res) && (int)bt.size() == c->n_buckets &&
-      fused_shape(c, th, cp, ra, res && c->opts.resident) == SOS_OK && set_bucket_teams(c, bt) == SOS_OK)
-    return SOS_OK;
+  if (!partial && tune_lookup(key, &th, &cp, &bt, &ra, &res) && (int)bt.size() == c->n_buckets) {
+    ChipPlan plan;
+    if (res == 3) {
+      if (std::count(bt.begin(), bt.end(), bt[0]) == (ptrdiff_t)bt.size() && chip_plan(c, bt[0], &plan) &&
+          set_bucket_teams(c, bt) == SOS_OK) {
+        chip_shape(c);
+        return SOS_OK;
+      }
+    } else if (fused_shape(c, th, cp, ra, res && c->opts.resident) == SOS_OK && set_bucket_teams(c, bt) == SOS_OK) {
+      return SOS_OK;
+    }
+  }
   // block shapes are tuned unless fixed by opts.block, team sizes unless fixed by opts.team
   std::vector<Shape> shapes;
   if (c->opts.block) shapes.push_back({c->fused_threads, c->fused_cpt, c->fused_ra, c->fused_res});
@@ -1059,7 +1207,7 @@ int autotune(sos_ctx* c) {
   std::vector<int> teams;
   if (c->opts.team) teams.push_back(c->opts.team);
   else
-    for (int t : {1, 2, 4, 8})
+    for (int t : {1, 2, 3, 4, 6, 8})
       if (team_ok(t, -1)) teams.push_back(t);
   hipStream_t st = c->stream;
   if (int rc0 = zero_directions(c)) return rc0;
@@ -1078,7 +1226,7 @@ int autotune(sos_ctx* c) {
     for (int rep = 0; rep < 3; ++rep) {
       HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
       HIPCHK(launch_residual(c->dev, c->seg.L, c->fp32, false, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part,
-                             c->fused_team > 1 ? c->team_part : nullptr, st));
+                             c->fused_team > 1 ? c->team_part : nullptr, queue_of(c), st));
       HIPCHK(hipEventRecord(e0, st));
       if (launch_fused_cg(c->dev, c->seg.L, c->fp32, c->fused_threads, c->fused_cpt, c->fused_lds, fused_args(c),
                           st) != hipSuccess) {
@@ -1104,8 +1252,18 @@ int autotune(sos_ctx* c) {
   int rc = SOS_OK;
   for (int team : teams)
     for (auto& cd : shapes) {
-      if (fused_shape(c, cd.threads, cd.cpt, cd.ra, cd.res) != SOS_OK || set_team(c, team) != SOS_OK) continue;
-      if (cd.res && !fused_args(c).res) continue;  // p and x do not fit in LDS with this team
+      ChipPlan plan;
+      if (cd.res == 3) {
+        if (!chip_plan(c, team, &plan)) continue;
+        chip_shape(c);
+        if (set_team(c, team) != SOS_OK) continue;
+      } else {
+        // (teams of three and six: the on-chip form only, whose blocks hold
+        // a third of 33 planes)
+        if ((team == 3 || team == 6) && !c->opts.team) continue;
+        if (fused_shape(c, cd.threads, cd.cpt, cd.ra, cd.res) != SOS_OK || set_team(c, team) != SOS_OK) continue;
+        if (cd.res && !fused_args(c).res) continue;  // p and x do not fit in LDS with this team
+      }
       double ms = INFINITY;
       if ((rc = time_config(&ms))) break;
       if (ms < best * kTuneMargin) {
@@ -1117,7 +1275,7 @@ int autotune(sos_ctx* c) {
   // per-bucket team sizes with the best shape: two passes of coordinate
   // descent, smallest bucket first (shrinking the small subdomains' teams
   // frees co-resident blocks that the large ones' teams then need)
-  if (!rc && c->n_buckets > 1 && !c->opts.team && std::isfinite(best) &&
+  if (!rc && c->n_buckets > 1 && !c->opts.team && std::isfinite(best) && bs.res != 3 &&
       fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res) == SOS_OK) {
     for (int pass = 0; pass < 2 * c->n_buckets && !rc; ++pass) {
       const int b = c->n_buckets - 1 - pass % c->n_buckets;
@@ -1141,7 +1299,12 @@ int autotune(sos_ctx* c) {
   if (rc) return rc;
   HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
   HIPCHK(hipStreamSynchronize(st));
-  rc = fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res);
+  if (bs.res == 3) {
+    chip_shape(c);
+    bs.threads = 0;
+  } else {
+    rc = fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res);
+  }
   if (!rc) rc = set_bucket_teams(c, bteams);
   if (rc) return rc;
   c->tune_ms = best;
@@ -1426,7 +1589,7 @@ int sos_setup_batch(const sos_mesh* mesh, const sos_partition* part, int32_t cop
       (rc = dalloc_v(&c->s1, c->n_local * es)) || (rc = dalloc(&c->part, 3 * c->seg.blocks.size())) ||
       (rc = dalloc(&c->part_norm, 2 * (size_t)c->n_norm_blocks)) || (rc = dalloc(&c->d_res, 4 + (size_t)copies)) ||
       (rc = dalloc(&c->scal, c->subs.size())) || (rc = dalloc(&c->ndone, 1)) || (rc = dalloc(&c->counters, 2)) ||
-      (rc = dalloc(&c->flags, 1)) ||
+      (rc = dalloc(&c->flags, 1)) || (rc = dalloc(&c->queue, 3)) ||
       (rc = dalloc(&c->team_part, c->subs.size() * kMaxTeam * 2 * 4))) {
     release(c);
     return rc;
@@ -1472,6 +1635,7 @@ int sos_setup_batch(const sos_mesh* mesh, const sos_partition* part, int32_t cop
   if (e == hipSuccess) e = hipMemset(c->lam, 0, std::max<int64_t>(1, c->n_lam) * sizeof(double));
   if (e == hipSuccess) e = hipMemset(c->rho, 0, c->n_local * sizeof(double));
   if (e == hipSuccess) e = hipMemset(c->flags, 0, sizeof(int32_t));
+  if (e == hipSuccess) e = hipMemset(c->queue, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     release(c);
@@ -1486,6 +1650,7 @@ int sos_set_robin(sos_ctx* c, const sos_robin* robin) {
   int rc = apply_robin(c, robin);
   if (rc) return rc;
   invalidate_graph(c);
+  if (c->fused_res == 3) c->fmap_dirty = true;  // the kernel with or without second-order terms
   hipError_t e = hipMemcpy(c->d_subs, c->subs.data(), c->subs.size() * sizeof(SubDesc), hipMemcpyHostToDevice);
   if (e == hipSuccess && !c->faces.empty())
     e = hipMemcpy(c->d_faces, c->faces.data(), c->faces.size() * sizeof(FaceDesc), hipMemcpyHostToDevice);
@@ -1537,6 +1702,15 @@ int sos_set_teams(sos_ctx* c, const int32_t* teams) {
   if (!c || !teams) return fail(SOS_EINVAL, "NULL argument");
   int rc = set_teams(c, std::vector<int32_t>(teams, teams + c->subs.size()));
   if (rc) return rc;
+  // the on-chip form takes one team size for all subdomains
+  if (c->fused_res == 3) {
+    ChipPlan plan;
+    bool same = true;
+    for (int32_t t : c->sub_team) same = same && t == c->sub_team[0];
+    if ((!same || !chip_plan(c, c->fused_team, &plan)) &&
+        (rc = fused_shape(c, c->opts.block, 0, c->opts.wave_rows, c->opts.resident)))
+      return rc;
+  }
   c->tuned = true;  // keep these teams and the current block shape
   return SOS_OK;
 }

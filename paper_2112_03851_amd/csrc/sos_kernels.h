@@ -81,10 +81,11 @@ hipError_t launch_load_nodes(const Dev& d, int max_n, const double* f_nodes, dou
 // b = f), in bx on the x-boundary nodes (SubDesc::xoff) and in b elsewhere;
 // then r = b - A u (FP64 apply), stored as Tr; partials (r'D^-1 r if rz, else
 // 0), r'r, b'b per block. team_part (optional): the fused kernel's team
-// slots, n_sub * kMaxTeam * 8 doubles, cleared for the launch that follows.
+// slots, n_sub * kMaxTeam * 8 doubles, and queue (optional): its ticket and
+// job counters, both cleared for the launch that follows, which is counted.
 hipError_t launch_residual(const Dev& d, const SegLaunch& L, int fp32, bool rz, const double* u,
                            const double* f, const double* lam, double* b, double* bx, void* r_out, double* part,
-                           double* team_part, hipStream_t st);
+                           double* team_part, int32_t* queue, hipStream_t st);
 // Why a subdomain's inner solve stopped early, OR-ed into one device word
 // per solve (the host reads it at every convergence check).
 enum BreakBits : int32_t {
@@ -134,13 +135,40 @@ struct FusedArgs {
                                     // the residual kernel before each launch)
   int32_t zu;                       // every block marches one segment (uniform z variant)
   int32_t rows;                     // wave-owned rows (see ra_rows): one barrier per plane
-  int32_t res;                      // resident in LDS (FP32, uniform z only): 1 p and x, 2 x
+  int32_t res;                      // resident in LDS (FP32, uniform z only): 1 p and x, 2 x; 3: on-chip form
   uint32_t lds_bytes;               // dynamic LDS of the launch (march planes + resident p, x)
   int32_t* flags;                   // BreakBits of the solve, OR-ed by every block that stops early
   uint64_t spin_ticks;              // team barrier: longest wait (wall clock ticks, 100 MHz)
+  // on-chip form (res == 3, sos_chip.h)
+  int32_t* queue;                   // [0] block tickets, [1] jobs taken (cleared by the residual kernel), [2] launches (it counts)
+  int32_t n_jobs, n_teams;          // subdomains, teams of the grid
+  int32_t chip_planes, chip_pairs;  // kernel variant: planes per block, pairs per row (0: any)
+  int32_t chip_wl;                  // kernel variant: w in LDS
+  int32_t chip_slots;               // most pairs of a plane of any subdomain
+  void *chip_w, *chip_x, *chip_halo, *chip_mail;  // private w, x, halo r and s, exchanged edge planes
   int32_t tag_skew;                 // team barrier: 0; 1 waits for a tag no member writes, so
                                     // every wait ends at spin_ticks (failure-handling tests)
 };
+// On-chip form of the fused kernel (sos_chip.h). Pairs (a vertex and the
+// mid-point after it) of a row of n nodes whose first has closure index klo;
+// rows of np pairs that a wave owns, one idle lane between two rows.
+constexpr int kChipThreads = 768;  // largest block: 11 waves of rows and one for the sums, 168 VGPRs
+__host__ __device__ inline int chip_pairs(int n, int klo) { return (klo + n - 1) / 2 + 1; }
+__host__ __device__ inline int chip_rows(int np) { return 65 / (np + 1); }
+__host__ __device__ inline size_t chip_even(size_t n) { return (n + 1) & ~size_t(1); }  // 16-byte steps of pairs
+// Dynamic LDS bytes: p, x (and w) of zlen planes and two operand planes.
+__host__ __device__ inline size_t chip_lds(int np, int ny, int zlen, size_t es, bool wl) {
+  const size_t n = (size_t)zlen * np * ny;
+  return ((wl ? 2 * chip_even(n) : 0) + 4 * n + (size_t)4 * np * (ny + 4)) * es;
+}
+constexpr int kChipAhead = 2;  // planes of w read ahead from the private buffer
+constexpr int kChipPrivate = 5;  // private 4-value records per thread: r, s of four halo planes, the ends' diagonal
+constexpr size_t kChipStatic = 1024;  // room for its static LDS
+// Launches the variant (a.chip_planes, a.chip_pairs, a.chip_wl) on a.n_teams
+// teams; per_cu != NULL: launch nothing, report how many of its blocks a
+// compute unit holds.
+hipError_t launch_chip(const Dev& d, const SegLaunch& L, int fp32, int threads, const FusedArgs& a, hipStream_t st,
+                       int* per_cu = nullptr);
 // lds: the march planes; with a.res the launch takes a.lds_bytes (march planes
 // and the resident p and x of the largest z-range, at least lds). A team
 // launch is a plain one when the kernel's occupancy admits the whole grid,

@@ -624,32 +624,32 @@ hipError_t launch_load_nodes(const Dev& d, int max_n, const double* f_nodes, dou
 
 hipError_t launch_residual(const Dev& d, const SegLaunch& L, int fp32, bool rz, const double* u, const double* f,
                            const double* lam, double* b, double* bx, void* r_out, double* part, double* team_part,
-                           hipStream_t st) {
+                           int32_t* queue, hipStream_t st) {
   SOS_DISPATCH_Q(d.hasq, {
   if (fp32 && rz && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, true, true>), dim3(L.nblocks),
                                                dim3(L.threads), L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out,
-                                               part, team_part));
+                                               part, team_part, queue));
   } else if (fp32 && rz) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, true>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part, queue));
   } else if (fp32 && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, false, true>), dim3(L.nblocks),
                                                dim3(L.threads), L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part,
-                                               team_part));
+                                               team_part, queue));
   } else if (fp32) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, false>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part, queue));
   } else if (rz && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<double, C, Q, true, true>), dim3(L.nblocks),
                                                dim3(L.threads), L.lds64, st, d, L.blocks, u, f, lam, b, bx,
-                                               (double*)r_out, part, team_part));
+                                               (double*)r_out, part, team_part, queue));
   } else if (rz) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<double, C, Q, true>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part, queue));
   } else {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<double, C, Q, false>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part, queue));
   }
   });
   return hipGetLastError();
@@ -723,6 +723,13 @@ hipError_t launch_add_correction(const Dev& d, const SegLaunch& L, int fp32, dou
 
 hipError_t launch_fused_cg(const Dev& d, const SegLaunch& L, int fp32, int threads, int cpt, size_t lds,
                            const FusedArgs& a, hipStream_t st, bool* plain) {
+  if (a.res == 3) {  // its teams form as blocks start: always a plain launch
+    if (plain) {
+      *plain = true;
+      return hipSuccess;
+    }
+    return launch_chip(d, L, fp32, threads, a, st);
+  }
   if (a.res && (!fp32 || !a.zu || lds > a.lds_bytes)) return hipErrorInvalidValue;
   SOS_DISPATCH_CPT(cpt, return launch_fused_cpt<C>(d, L, fp32, threads, lds, a, st, plain));
   return hipSuccess;

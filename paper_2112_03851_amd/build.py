@@ -8,6 +8,7 @@ library next to this file.
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -41,12 +42,64 @@ def _flags():
             "-I", os.path.join(ROOT, "include")]
 
 
+def masked_spills(asm: str) -> list[tuple[str, str]]:
+    """Vector instructions that the compiler put between the label of a block
+    where lanes come together again (the target of s_cbranch_execz) and that
+    block's restore of the lane mask, as (kernel, instruction). A register spill
+    or copy there moves only the lanes that took the branch, none after a loop
+    that every lane left, and the others read garbage later on."""
+    joins = set(re.findall(r"s_cbranch_execz (\.LBB\w+)", asm))
+    found, kernel, join, seen = [], "", False, []
+    for line in asm.split("\n"):
+        label = re.match(r"(_Z\w+|\.LBB\w+):", line)
+        if label:
+            if label[1].startswith("_Z"):
+                kernel = label[1]
+            join, seen = label[1] in joins, []
+            continue
+        text = line.split(";")[0].strip()
+        if line.startswith("; %bb."):
+            join = False
+        elif not join or not text or text.startswith("."):
+            continue
+        elif text.startswith("s_or_b64 exec, exec"):
+            found += [(kernel, t) for t in seen]
+            join = False
+        elif "exec" in text or text.startswith(("s_branch", "s_cbranch", "s_barrier")):
+            join = False
+        elif not text.startswith(("s_", "v_writelane", "v_readlane", "v_readfirstlane")):
+            seen.append(text)
+    return found
+
+
 def _compile(unit, verbose):
     src, defs, obj = unit
-    cmd = [hipcc(), *_flags(), *defs, "-c", os.path.join(CSRC, src), "-o", os.path.join(OBJDIR, obj)]
+    out = os.path.join(OBJDIR, obj)
+    cmd = [hipcc(), *_flags(), *defs, "-c", os.path.join(CSRC, src), "-o", out]
+    device = src.endswith(".hip")
+    if device:  # keep the kernels' assembly, in a folder of the unit's own
+        tmp = out + ".tmp"
+        shutil.rmtree(tmp, ignore_errors=True)
+        os.makedirs(tmp)
+        cmd[-1] = os.path.join(tmp, "unit.o")
+        cmd.append("-save-temps=obj")
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
+    if device and res.returncode == 0:
+        bad = []
+        asm = [name for name in os.listdir(tmp) if ARCH in name and name.endswith(".s")]
+        if not asm:
+            raise RuntimeError("no assembly of " + src)
+        for name in asm:
+            with open(os.path.join(tmp, name)) as f:
+                bad += masked_spills(f.read())
+        if bad:
+            res.returncode = 1
+            res.stderr += "vector registers moved under a partial lane mask:\n" + "".join(f"  {k}: {t}\n" for k, t in bad)
+        else:
+            os.replace(os.path.join(tmp, "unit.o"), out)
+        shutil.rmtree(tmp, ignore_errors=True)
     return cmd, res
 
 

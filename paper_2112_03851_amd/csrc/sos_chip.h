@@ -427,7 +427,8 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
           r_at(h < 2 ? zb0 - nlo + h : zb1 + h - 2, va, vb);
           hrs[h * nthreads + tid] = P4<T>{va, vb, z, z};
         }
-        for (int i = tid; i < 2 * opn; i += nthreads) opl[i] = P2<T>{z, z};
+        for (int i0 = 0; i0 < 2 * opn; i0 += nthreads)  // (uniform trips, see lds_zero)
+          if (i0 + tid < 2 * opn) opl[i0 + tid] = P2<T>{z, z};
       }
       __syncthreads();
       // LDS addresses: two rows below this pair's place in the first operand

@@ -291,7 +291,14 @@ __device__ __forceinline__ T slot_dinv(const Slots<T, CPT, Q>& sl, int m, int k)
 
 template <typename T>
 __device__ __forceinline__ void lds_zero(T* lds, int n) {
-  for (int e = threadIdx.x; e < n; e += blockDim.x) lds[e] = T(0);
+  // The trip count is the same in every lane. Where lanes leave a loop one by
+  // one, the block after it first restores the lane mask, and under register
+  // pressure the compiler has put spills before that restore: they then store
+  // no lane, and every later reload is garbage. (build.py looks for such spills.)
+  for (int e0 = 0; e0 < n; e0 += blockDim.x) {
+    const int e = e0 + threadIdx.x;
+    if (e < n) lds[e] = T(0);
+  }
 }
 
 // The z-march, software-pipelined: fetch(li) issues the global loads of the

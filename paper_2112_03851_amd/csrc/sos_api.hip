@@ -287,12 +287,13 @@ int build_seg(sos_ctx* c) {
     int chunks = std::min(want, std::max(1, nz / kMinSeg));
     int len = (nz + chunks - 1) / chunks;
     for (int z = 0; z < nz; z += len) {
-      BlockDesc b{s, z, std::min(nz, z + len), 0};
+      BlockDesc b{s, z, std::min(nz, z + len), g.bfirst.back(), 0, {0, 0, 0}};
       g.blocks.push_back(b);
       zu = zu && march_segments(d.n[0], d.n[1], b.z1 - b.z0, threads, cpt) == 1;
       lds64 = std::max(lds64, march_lds_bytes(d.n[0], d.n[1], b.z1 - b.z0, threads, cpt, 8));
       lds32 = std::max(lds32, march_lds_bytes(d.n[0], d.n[1], b.z1 - b.z0, threads, cpt, 4));
     }
+    for (size_t b = g.bfirst.back(); b < g.blocks.size(); ++b) g.blocks[b].b1 = (int32_t)g.blocks.size();
     g.bfirst.push_back((int32_t)g.blocks.size());
   }
   if (lds64 + kMarchStatic > c->lds_limit)

@@ -49,24 +49,6 @@ __device__ __forceinline__ T from_below(T v) { return lane_move<0x138>(v); }
 template <typename T>
 __device__ __forceinline__ T from_above(T v) { return lane_move<0x130>(v); }
 
-// Sum over the wave in a fixed order, valid in lane 63 (row shifts, then the
-// row broadcasts of lanes 15 and 31).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
-  return v + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_sum63(double v) {
-  v = dpp_add<0x111, 0xf>(v);
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  v = dpp_add<0x118, 0xf>(v);
-  v = dpp_add<0x142, 0xa>(v);
-  v = dpp_add<0x143, 0xc>(v);
-  return v;
-}
-
 // A value that is the same in every lane, moved to scalar registers. (Without
 // the empty asm the compiler folds the builtin away where it knows the value to
 // be uniform, and keeps what the vector unit computed in vector registers. The
@@ -171,14 +153,6 @@ struct ChipRed {
   int fail;
   int job;
 };
-
-// Sum over the 16 lanes of a row, valid in its last lane.
-__device__ __forceinline__ double row_sum15(double v) {
-  v = dpp_add<0x111, 0xf>(v);
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  return dpp_add<0x118, 0xf>(v);
-}
 
 template <int N, class F>
 __device__ __forceinline__ void chip_sum(double (&v)[N], ChipRed& sh, const FusedArgs& a, int s, int tau, int TM,
@@ -298,11 +272,9 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
         (ny + R - 1) / R >= (int)(blockDim.x >> 6) || chip_lds(np, ny, zmax, sizeof(T), WL) > a.lds_bytes ||
         nslots > a.chip_slots)
       brk |= kBrkLaunch;  // (the host sizes the launch for every subdomain)
-    double rr = 0.0, bb = 0.0;
-    for (int b = bfirst[s]; b < bfirst[s + 1]; ++b) {
-      rr += a.res_part[3 * b + 1];
-      bb += a.res_part[3 * b + 2];
-    }
+    double rb[2];
+    part_sums<1>(a.res_part, bfirst[s], bfirst[s + 1], rb);
+    const double rr = rb[0], bb = rb[1];
     const double stop2 =
         uniform(fmax(uniform(a.tol_rel * a.tol_rel) * rr, uniform(a.tol_abs * a.tol_abs) * bb));
     // the inner solve runs on sig r, sig a power of two (see k_fused_cg)

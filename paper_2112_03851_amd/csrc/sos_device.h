@@ -25,7 +25,7 @@
 // CG (Sec. 6: diagonal preconditioner). Each iteration is two passes:
 //   A: p = D^-1 r + beta p_old (recomputed on halo planes), q = A p, p'q
 //   B: x += alpha p, r -= alpha q, r'z, r'r  (pointwise)
-// Reductions are wave64 shuffles, then a fixed-order sum over waves and over
+// Reductions are lane moves within a wave, then a fixed-order sum over waves and over
 // the blocks of a subdomain: results are bitwise repeatable.
 #pragma once
 
@@ -105,31 +105,70 @@ __device__ __forceinline__ int row_kind(int c, int ne2) {
 
 // ---------------------------------------------------------------------------- reductions
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Sum over the wave in a fixed order, valid in lane 63 (row shifts, then the
+// row broadcasts of lanes 15 and 31).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum63(double v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);
+  v = dpp_add<0x143, 0xc>(v);
   return v;
 }
+// Sum over the 16 lanes of a row, valid in its last lane.
+__device__ __forceinline__ double row_sum15(double v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  return dpp_add<0x118, 0xf>(v);
+}
+// A lane's value in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
 
-// Sum N values over the block; every thread receives the sums (fixed order).
+// Sum N values over the block; every thread receives the sums (fixed order:
+// the lanes of each wave, then the waves, both by lane moves in registers).
 template <int N>
 __device__ __forceinline__ void block_sum(double (&v)[N]) {
   __shared__ double red[N * 16];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
-  for (int n = 0; n < N; ++n) v[n] = wave_sum(v[n]);
+  for (int n = 0; n < N; ++n) v[n] = wave_sum63(v[n]);
   __syncthreads();
-  if (lane == 0) {
+  if (lane == 63) {
 #pragma unroll
     for (int n = 0; n < N; ++n) red[n * 16 + w] = v[n];
   }
   __syncthreads();
+  const int k = lane & 15;
 #pragma unroll
-  for (int n = 0; n < N; ++n) {
-    double s = 0.0;
-    for (int k = 0; k < nw; ++k) s += red[n * 16 + k];
-    v[n] = s;
+  for (int n = 0; n < N; ++n) v[n] = lane_value(row_sum15(k < nw ? red[n * 16 + k] : 0.0), 15);
+}
+
+// Sums of the partials of blocks [b0, b1) (three words a block, N of them from
+// word FIRST on), one lane a block: their loads are in flight together, where a
+// loop over the blocks waits for one after the other. Every thread of the wave
+// receives the sums.
+template <int FIRST, int N>
+__device__ __forceinline__ void part_sums(const double* part, int b0, int b1, double (&v)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] = 0.0;
+  for (int c = b0; c < b1; c += 64) {  // (uniform trips, see lds_zero)
+    const int b = c + (int)(threadIdx.x & 63);
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] += b < b1 ? part[3 * b + FIRST + n] : 0.0;
   }
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] = lane_value(wave_sum63(v[n]), 63);
 }
 
 // ---------------------------------------------------------------------------- march geometry
@@ -860,10 +899,14 @@ __device__ __forceinline__ void cg_pass_b(const Slots<T, CPT, Q>& sl, bool first
 
 // ---------------------------------------------------------------------------- stepwise CG
 
-
+// Bound, on a small problem, by the chain of dependent loads before a block's
+// first plane: block, subdomain state, the partials of the subdomain's blocks.
+// They are now in flight together and the partials summed by lanes: a whole
+// plain solve went from 214 to 196 ms (32^3 elements, 8 subdomains, 32 blocks)
+// and from 786 to 747 ms (64^3, 64 subdomains, 256 blocks).
 template <typename T, int CPT, bool Q, bool ZU = false>
-__global__ void __launch_bounds__(Bound<CPT>::value) k_cg_apply(Dev d, const BlockDesc* blocks, const int32_t* __restrict__ bfirst,
-                                                   int t, int max_inner, const T* __restrict__ r,
+__global__ void __launch_bounds__(Bound<CPT>::value) k_cg_apply(Dev d, const BlockDesc* blocks, int t,
+                                                   int max_inner, const T* __restrict__ r,
                                                    const T* __restrict__ pold, T* __restrict__ pnew,
                                                    T* __restrict__ q, double* __restrict__ part,
                                                    CgScal* __restrict__ scal, int32_t* ndone,
@@ -872,38 +915,32 @@ __global__ void __launch_bounds__(Bound<CPT>::value) k_cg_apply(Dev d, const Blo
   T* lds = reinterpret_cast<T*>(smem);
   const BlockDesc bd = blocks[blockIdx.x];
   const int s = bd.s;
-  if (scal[s].done) return;
-  const int b0 = bfirst[s], b1 = bfirst[s + 1];
-  const bool leader = ((int)blockIdx.x == b0) && (threadIdx.x == 0);
-  double rz, rr;
-  if (t == 0) {
-    rz = scal[s].rz[0];
-    rr = scal[s].rr0;
-  } else {
-    rz = 0.0;
-    rr = 0.0;
-    for (int b = b0; b < b1; ++b) {
-      rz += part[3 * b + 1];
-      rr += part[3 * b + 2];
-    }
-  }
+  // All the block needs to know is loaded before the first wait, and before the
+  // first store: the loads then go through the scalar cache, and the
+  // descriptor stays in scalar registers.
+  const SubDesc sd = d.subs[s];
+  const double rz0 = scal[s].rz[0], rz1 = scal[s].rz[1], rr0 = scal[s].rr0, stop2 = scal[s].stop2;
+  const int32_t done = scal[s].done;
+  double zr[2] = {rz0, rr0};
+  if (t != 0) part_sums<1>(part, bd.b0, bd.b1, zr);
+  if (done) return;
+  const bool leader = ((int)blockIdx.x == bd.b0) && (threadIdx.x == 0);
+  const double rz = zr[0], rr = zr[1];
   const bool bad = !isfinite(rr) || !isfinite(rz);
-  if (bad || !(rr > scal[s].stop2) || t >= max_inner) {
+  if (bad || !(rr > stop2) || t >= max_inner) {
     if (leader) {
       scal[s].done = 1;
       scal[s].iters = t;
       scal[s].breakdown = bad ? kBrkNonFinite : 0;
       if (bad) atomicOr(flags, kBrkNonFinite);
       atomicAdd(ndone, 1);
-      const SubDesc& sd = d.subs[s];
       atomicAdd(&counters[0], (unsigned long long)t);
       atomicAdd(&counters[1], cg_bytes(sd, t, sizeof(T)));
     }
     return;
   }
-  const double beta = t == 0 ? 0.0 : rz / scal[s].rz[(t - 1) & 1];
+  const double beta = t == 0 ? 0.0 : rz / ((t & 1) != 0 ? rz0 : rz1);
   if (leader) scal[s].rz[t & 1] = rz;
-  const SubDesc sd = d.subs[s];
   Slots<T, CPT, Q> sl;
   slots_init(sl, sd, d.geo, bd.z0, bd.z1, true);
   lds_zero(lds, sl.G * kPlanes * sl.SP);
@@ -937,19 +974,21 @@ __global__ void __launch_bounds__(Bound<CPT>::value) k_cg_apply(Dev d, const Blo
 }
 
 template <typename T, int CPT, bool Q>
-__global__ void __launch_bounds__(Bound<CPT>::value) k_cg_update(Dev d, const BlockDesc* blocks, const int32_t* __restrict__ bfirst,
-                                                    int t, T* __restrict__ x, const T* __restrict__ p,
+__global__ void __launch_bounds__(Bound<CPT>::value) k_cg_update(Dev d, const BlockDesc* blocks, int t, T* __restrict__ x, const T* __restrict__ p,
                                                     T* __restrict__ r, const T* __restrict__ q,
                                                     double* __restrict__ part, CgScal* __restrict__ scal,
                                                     int32_t* ndone, int32_t* flags) {
   const BlockDesc bd = blocks[blockIdx.x];
   const int s = bd.s;
-  if (scal[s].done) return;
-  const int b0 = bfirst[s], b1 = bfirst[s + 1];
-  double pq = 0.0;
-  for (int b = b0; b < b1; ++b) pq += part[3 * b];
+  const SubDesc sd = d.subs[s];  // (loads before the first wait, see k_cg_apply)
+  const double rz = (t & 1) != 0 ? scal[s].rz[1] : scal[s].rz[0];
+  const int32_t done = scal[s].done;
+  double pqs[1];
+  part_sums<0>(part, bd.b0, bd.b1, pqs);
+  if (done) return;
+  const double pq = pqs[0];
   if (!(pq > 0.0) || !isfinite(pq)) {
-    if ((int)blockIdx.x == b0 && threadIdx.x == 0) {
+    if ((int)blockIdx.x == bd.b0 && threadIdx.x == 0) {
       const int32_t why = isfinite(pq) ? kBrkCurvature : kBrkNonFinite;
       scal[s].done = 1;
       scal[s].iters = t;
@@ -959,8 +998,7 @@ __global__ void __launch_bounds__(Bound<CPT>::value) k_cg_update(Dev d, const Bl
     }
     return;
   }
-  const T alpha = T(scal[s].rz[t & 1] / pq);
-  const SubDesc sd = d.subs[s];
+  const T alpha = T(rz / pq);
   Slots<T, CPT, Q> sl;
   slots_init(sl, sd, d.geo, bd.z0, bd.z1, true);
   double a0 = 0.0, a1 = 0.0;
@@ -1146,11 +1184,10 @@ __global__ void __launch_bounds__(Bound<CPT>::value) k_fused_cg(Dev d, const int
   T* const p0b = reinterpret_cast<T*>(a.p0);
   T* const p1b = reinterpret_cast<T*>(a.p1);
   T* __restrict__ x = reinterpret_cast<T*>(a.x);
-  double rr = 0.0, bb = 0.0;
-  for (int b = bfirst[s]; b < bfirst[s + 1]; ++b) {
-    rr += a.res_part[3 * b + 1];
-    bb += a.res_part[3 * b + 2];
-  }
+  double rb[2];
+  part_sums<1>(a.res_part, bfirst[s], bfirst[s + 1], rb);
+  double rr = rb[0];
+  const double bb = rb[1];
   const double stop2 = fmax(a.tol_rel * a.tol_rel * rr, a.tol_abs * a.tol_abs * bb);
   // The inner solve runs on sig r instead of r, sig a power of two that brings
   // the mean square of r near one: exact scaling, undone when x is added to u.

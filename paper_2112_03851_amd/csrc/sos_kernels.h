@@ -5,9 +5,11 @@
 
 namespace sos {
 
-// A block of a segmented launch: subdomain s, z-range [z0, z1) of its planes.
+// A block of a segmented launch: subdomain s, z-range [z0, z1) of its planes;
+// the blocks of s are [b0, b1) (here too, so that a kernel that sums their
+// partials needs no second table first).
 struct BlockDesc {
-  int32_t s, z0, z1, pad;
+  int32_t s, z0, z1, b0, b1, pad[3];
 };
 
 // Launch geometry of a segmented launch (one block per BlockDesc).

@@ -669,22 +669,22 @@ hipError_t launch_cg_apply(const Dev& d, const SegLaunch& L, int fp32, int t, in
   SOS_DISPATCH_Q(d.hasq, {
   if (fp32 && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_cg_apply<float, C, Q, true>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds32, st, d, L.blocks, L.bfirst, t, max_inner, (const float*)r,
+                                               L.lds32, st, d, L.blocks, t, max_inner, (const float*)r,
                                                (const float*)p_old, (float*)p_new, (float*)q, part, scal, ndone,
                                                counters, flags));
   } else if (fp32) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_cg_apply<float, C, Q>), dim3(L.nblocks), dim3(L.threads), L.lds32,
-                                               st, d, L.blocks, L.bfirst, t, max_inner, (const float*)r,
+                                               st, d, L.blocks, t, max_inner, (const float*)r,
                                                (const float*)p_old, (float*)p_new, (float*)q, part, scal, ndone,
                                                counters, flags));
   } else if (L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_cg_apply<double, C, Q, true>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, L.bfirst, t, max_inner, (const double*)r,
+                                               L.lds64, st, d, L.blocks, t, max_inner, (const double*)r,
                                                (const double*)p_old, (double*)p_new, (double*)q, part, scal,
                                                ndone, counters, flags));
   } else {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_cg_apply<double, C, Q>), dim3(L.nblocks), dim3(L.threads), L.lds64,
-                                               st, d, L.blocks, L.bfirst, t, max_inner, (const double*)r,
+                                               st, d, L.blocks, t, max_inner, (const double*)r,
                                                (const double*)p_old, (double*)p_new, (double*)q, part, scal,
                                                ndone, counters, flags));
   }
@@ -698,11 +698,11 @@ hipError_t launch_cg_update(const Dev& d, const SegLaunch& L, int fp32, int t, v
   SOS_DISPATCH_Q(d.hasq, {
   if (fp32) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_cg_update<float, C, Q>), dim3(L.nblocks), dim3(L.threads), 0, st, d,
-                                               L.blocks, L.bfirst, t, (float*)x, (const float*)p, (float*)r,
+                                               L.blocks, t, (float*)x, (const float*)p, (float*)r,
                                                (const float*)q, part, scal, ndone, flags));
   } else {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_cg_update<double, C, Q>), dim3(L.nblocks), dim3(L.threads), 0, st, d,
-                                               L.blocks, L.bfirst, t, (double*)x, (const double*)p, (double*)r,
+                                               L.blocks, t, (double*)x, (const double*)p, (double*)r,
                                                (const double*)q, part, scal, ndone, flags));
   }
   });

@@ -277,6 +277,14 @@ int build_seg(sos_ctx* c) {
   int threads = ((smax + cpt - 1) / cpt + 63) / 64 * 64;
   const int n_sub = (int)c->subs.size();
   const int want = std::max(1, (2 * 256 + n_sub - 1) / n_sub);
+  // Segments of kMinSeg planes or more pay four extra planes each. Where they
+  // leave compute units idle, shorter ones down to two planes, at most one
+  // block a compute unit: a march's time is its number of planes then. 16^3
+  // elements in 4 subdomains 66.7 -> 63.1 ms a solve (16 -> 64 blocks), the plain
+  // form of 32^3 in 8 192 -> 138 ms (32 -> 128 blocks). Not past one block a
+  // unit: with 448 blocks for 256 the plain form of 64^3 in 64 subdomains went
+  // from 706 to 833 ms, FP32 solves of it from 673 to 704 ms.
+  const int spread = 256 / n_sub;
   g.blocks.clear();
   g.bfirst.assign(1, 0);
   size_t lds64 = 0, lds32 = 0;
@@ -284,7 +292,7 @@ int build_seg(sos_ctx* c) {
   for (int s = 0; s < n_sub; ++s) {
     const SubDesc& d = c->subs[s];
     const int nz = d.n[2];
-    int chunks = std::min(want, std::max(1, nz / kMinSeg));
+    int chunks = std::max(std::min(want, std::max(1, nz / kMinSeg)), std::min(spread, nz / 2));
     int len = (nz + chunks - 1) / chunks;
     for (int z = 0; z < nz; z += len) {
       BlockDesc b{s, z, std::min(nz, z + len), g.bfirst.back(), 0, {0, 0, 0}};

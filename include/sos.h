@@ -247,9 +247,11 @@ int sos_axes(const sos_ctx* ctx, int32_t* perm);
  * preconditioned CG; a team splits its z-planes and meets at one barrier per
  * CG iteration). The autotuner picks them per size bucket: subdomains whose
  * node counts differ by more than 1.5x fall into three buckets of equal
- * width in log size, each with its own team size. */
+ * width in log size, each with its own team size; with the form that keeps
+ * the whole state on the chip one size of up to 64 for all. */
 int sos_teams(const sos_ctx* ctx, int32_t* teams);
-/* Set them (1..8, at most the subdomain's z-planes; SOS_EINVAL otherwise):
+/* Set them (1..8, at most the subdomain's z-planes, or one larger size for all
+ * that the form with the whole state on the chip takes; SOS_EINVAL otherwise):
  * the current block shape and these teams are used from now on without
  * autotuning, until sos_set_opts changes a launch option. */
 int sos_set_teams(sos_ctx* ctx, const int32_t* teams);

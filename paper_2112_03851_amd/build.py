@@ -43,13 +43,14 @@ def _flags():
 
 
 def masked_spills(asm: str) -> list[tuple[str, str]]:
-    """Vector instructions that the compiler put between the label of a block
-    where lanes come together again (the target of s_cbranch_execz) and that
-    block's restore of the lane mask, as (kernel, instruction). A register spill
+    """Vector instructions that the compiler put between the head of a block
+    where lanes come together again (the target of s_cbranch_execz, the exit of a
+    loop that lanes leave one by one) and that block's restore of the lane mask,
+    as (kernel, instruction). A register spill
     or copy there moves only the lanes that took the branch, none after a loop
     that every lane left, and the others read garbage later on."""
     joins = set(re.findall(r"s_cbranch_execz (\.LBB\w+)", asm))
-    found, kernel, join, seen = [], "", False, []
+    found, kernel, join, seen, loop_end = [], "", False, [], False
     for line in asm.split("\n"):
         label = re.match(r"(_Z\w+|\.LBB\w+):", line)
         if label:
@@ -58,8 +59,10 @@ def masked_spills(asm: str) -> list[tuple[str, str]]:
             join, seen = label[1] in joins, []
             continue
         text = line.split(";")[0].strip()
-        if line.startswith("; %bb."):
-            join = False
+        if text.startswith("s_cbranch_execnz"):  # falls through with no lane left
+            join, seen = True, []
+        elif line.startswith("; %bb."):
+            join = join and loop_end
         elif not join or not text or text.startswith("."):
             continue
         elif text.startswith("s_or_b64 exec, exec"):
@@ -69,6 +72,7 @@ def masked_spills(asm: str) -> list[tuple[str, str]]:
             join = False
         elif not text.startswith(("s_", "v_writelane", "v_readlane", "v_readfirstlane")):
             seen.append(text)
+        loop_end = text.startswith("s_cbranch_execnz") or (loop_end and not text)
     return found
 
 

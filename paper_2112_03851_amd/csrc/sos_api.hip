@@ -88,7 +88,7 @@ struct ChipPlan {
   int planes = 0, pairs = 0, wl = 0;  // kernel variant
   int threads = 0, slots = 0;         // block size, most pairs of a plane
   int team = 0, n_teams = 0;          // blocks per subdomain, teams of the grid
-  size_t lds = 0, w = 0, x = 0, halo = 0, mail = 0;  // dynamic LDS, workspace bytes
+  size_t lds = 0, part = 0, w = 0, x = 0, halo = 0, mail = 0;  // dynamic LDS, workspace bytes
 };
 
 struct sos_ctx {
@@ -365,8 +365,12 @@ int fused_shape(sos_ctx* c, int threads, int cpt = 0, int ra = 0, int res = 0) {
   return SOS_OK;
 }
 
-// The on-chip form (its launch follows from the team size, chip_plan).
-void chip_shape(sos_ctx* c) {
+// The on-chip form with one team size for all subdomains (chip_plan has
+// checked it; the launch follows from it).
+void chip_shape(sos_ctx* c, int team) {
+  c->sub_team.assign(c->subs.size(), team);
+  c->fused_team = team;
+  invalidate_graph(c);
   c->fused_cpt = 2;  // a thread's columns: one pair of x-neighbours
   c->fused_ra = 1;
   c->fused_res = 3;
@@ -444,7 +448,7 @@ int dalloc_v(void** p, size_t bytes);
 // kernel variant holds; w in LDS where it fits beside p and x; as many teams
 // as the GPU holds at once.
 bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
-  if (!c->opts.resident) return false;
+  if (!c->opts.resident || team < 1 || team > kMaxChipTeam) return false;
   const size_t es = c->fp32 ? 4 : 8;
   ChipPlan p;
   p.team = team;
@@ -478,8 +482,9 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   p.wl = lds_of(true) <= limit;
   p.lds = lds_of(p.wl);
   if (p.lds > limit) return false;
-  p.planes = zmax <= 5 ? 5 : (zmax <= 9 ? 9 : (zmax <= 12 ? 12 : 17));
-  if (zmax > p.planes || (!c->fp32 && p.planes > 5) || (p.planes < 17 && !p.wl)) return false;
+  for (int planes : kChipPlanes)
+    if (zmax <= planes && !p.planes) p.planes = planes;
+  if (!p.planes || (!c->fp32 && p.planes > 5) || (p.planes < 17 && !p.wl)) return false;
   FusedArgs a = {};
   a.team = team;
   a.chip_planes = p.planes;
@@ -493,9 +498,15 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
     (void)hipGetLastError();
     return false;
   }
+  // three waves a SIMD (the kernel's registers), and a block's waves start at
+  // the same SIMD each time: blocks of five to eight waves do not fit twice,
+  // which the occupancy query does not see
+  const int simd_waves = (p.threads / 64 + 3) / 4;
+  per_cu = std::min(per_cu, std::max(1, kChipThreads / 256 / simd_waves));
   p.n_teams = std::min((int)c->subs.size(), per_cu * cus / team);
   if (p.n_teams < 1) return false;
   const size_t blocks = (size_t)p.n_teams * team;
+  p.part = align64((int64_t)c->subs.size() * team) * 2 * 4 * sizeof(double);
   p.w = p.wl ? 0 : blocks * (p.planes + kChipAhead) * p.threads * 2 * es;
   p.x = p.planes > 12 ? blocks * (p.planes + kChipAhead) * p.threads * 2 * es : 0;
   p.halo = blocks * kChipPrivate * p.threads * 4 * es;
@@ -519,7 +530,7 @@ int ensure_fmap(sos_ctx* c) {
     // one entry per subdomain: the order in which the teams take them
     if (!chip_plan(c, c->fused_team, &c->chip)) return fail(SOS_EINVAL, "the on-chip fused kernel does not fit team %d", c->fused_team);
     c->fused_threads = c->chip.threads;
-    const size_t need = c->chip.w + c->chip.x + c->chip.halo + c->chip.mail;
+    const size_t need = c->chip.part + c->chip.w + c->chip.x + c->chip.halo + c->chip.mail;
     if (need > c->chip_bytes) {
       HIPCHK(hipStreamSynchronize(c->stream));
       if (c->chip_ws) (void)hipFree(c->chip_ws);
@@ -590,7 +601,7 @@ std::vector<Shape> fused_candidates(const sos_ctx* c) {
     for (size_t i = 0; i < n; ++i) out.push_back({out[i].threads, out[i].cpt, out[i].ra, 1});
   }
   // (shapes with res = 1 keep p and x in LDS, or x alone where both do not fit)
-  // the on-chip form; it comes first: a near-equal other shape does not replace it
+  // the on-chip form (a near-equal other shape does not replace it)
   if (c->opts.resident) out.insert(out.begin(), Shape{0, 2, 1, 3});
   return out;
 }
@@ -859,6 +870,8 @@ FusedArgs fused_args(sos_ctx* c) {
     a.chip_wl = p.wl;
     a.chip_slots = p.slots;
     char* ws = static_cast<char*>(c->chip_ws);
+    a.team_part = static_cast<double*>(c->chip_ws);
+    ws += p.part;
     a.chip_w = ws;
     a.chip_x = ws + p.w;
     a.chip_halo = ws + p.w + p.x;
@@ -902,13 +915,21 @@ bool schedule_by_work(const sos_ctx* c) {
   return c->opts.schedule && c->fused_team <= 1 && c->fmap.size() == c->subs.size();
 }
 
+// Team partial sums that the residual kernel clears for the fused launch (null
+// where no team meets), and their doubles per subdomain.
+double* team_slots(sos_ctx* c) {
+  if (c->fused_team <= 1) return nullptr;
+  return c->fused_res == 3 ? static_cast<double*>(c->chip_ws) : c->team_part;
+}
+int team_words(const sos_ctx* c) { return (c->fused_res == 3 ? c->fused_team : kMaxTeam) * 2 * 4; }
+
 // The counters of the on-chip form, which the residual kernel clears (else null).
 int32_t* queue_of(sos_ctx* c) { return c->fused_res == 3 ? c->queue : nullptr; }
 
 int enqueue_batched_iteration(sos_ctx* c, hipEvent_t ev0, hipEvent_t ev1) {
   hipStream_t st = c->stream;
   HIPCHK(launch_residual(c->dev, c->seg.L, c->fp32, false, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part,
-                         c->fused_team > 1 ? c->team_part : nullptr, queue_of(c), st));
+                         team_slots(c), team_words(c), queue_of(c), st));
   if (ev0) HIPCHK(hipEventRecord(ev0, st));
   HIPCHK(launch_fused_cg(c->dev, c->seg.L, c->fp32, c->fused_threads, c->fused_cpt, c->fused_lds, fused_args(c), st));
   if (ev1) HIPCHK(hipEventRecord(ev1, st));
@@ -924,7 +945,7 @@ int enqueue_batched_iteration(sos_ctx* c, hipEvent_t ev0, hipEvent_t ev1) {
 int stepwise_iteration(sos_ctx* c) {
   hipStream_t st = c->stream;
   const SegLaunch& L = c->seg.L;
-  HIPCHK(launch_residual(c->dev, L, c->fp32, true, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part, nullptr, nullptr, st));
+  HIPCHK(launch_residual(c->dev, L, c->fp32, true, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part, nullptr, 0, nullptr, st));
   HIPCHK(launch_cg_init(c->dev, L, c->part, c->opts.inner_tol, c->opts.inner_abs, c->scal, c->ndone, st));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->opts.timing) {
@@ -1196,8 +1217,8 @@ int autotune(sos_ctx* c) {
     ChipPlan plan;
     if (res == 3) {
       if (std::count(bt.begin(), bt.end(), bt[0]) == (ptrdiff_t)bt.size() && chip_plan(c, bt[0], &plan) &&
-          set_bucket_teams(c, bt) == SOS_OK) {
-        chip_shape(c);
+          (!c->opts.team || bt[0] == c->opts.team)) {
+        chip_shape(c, bt[0]);
         return SOS_OK;
       }
     } else if (fused_shape(c, th, cp, ra, res && c->opts.resident) == SOS_OK && set_bucket_teams(c, bt) == SOS_OK) {
@@ -1215,9 +1236,21 @@ int autotune(sos_ctx* c) {
   };
   std::vector<int> teams;
   if (c->opts.team) teams.push_back(c->opts.team);
-  else
-    for (int t : {1, 2, 3, 4, 6, 8})
-      if (team_ok(t, -1)) teams.push_back(t);
+  else {
+    // For the on-chip form also the teams whose members fill the planes that a
+    // variant holds, and the one with a member for every compute unit. Few slabs
+    // of many planes need them: 8 of 383 planes of 15 x 27 nodes took 32.3 ms a
+    // solve with teams of eight (64 blocks, 256 units), 13.3 ms with 32.
+    std::vector<int> sizes = {1, 2, 3, 4, 6, 8};
+    int zmax = 1;
+    for (auto& s : c->subs) zmax = std::max(zmax, s.n[2]);
+    for (int planes : kChipPlanes) sizes.push_back((zmax + planes - 1) / planes);
+    sizes.push_back(256 / (int)c->subs.size());
+    std::sort(sizes.begin(), sizes.end());
+    sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
+    for (int t : sizes)
+      if (t >= 1 && t <= kMaxChipTeam && team_ok(t, -1)) teams.push_back(t);
+  }
   hipStream_t st = c->stream;
   if (int rc0 = zero_directions(c)) return rc0;
   // the trial launches solve the first outer iteration's problem: the
@@ -1235,7 +1268,7 @@ int autotune(sos_ctx* c) {
     for (int rep = 0; rep < 3; ++rep) {
       HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
       HIPCHK(launch_residual(c->dev, c->seg.L, c->fp32, false, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part,
-                             c->fused_team > 1 ? c->team_part : nullptr, queue_of(c), st));
+                             team_slots(c), team_words(c), queue_of(c), st));
       HIPCHK(hipEventRecord(e0, st));
       if (launch_fused_cg(c->dev, c->seg.L, c->fp32, c->fused_threads, c->fused_cpt, c->fused_lds, fused_args(c),
                           st) != hipSuccess) {
@@ -1255,7 +1288,11 @@ int autotune(sos_ctx* c) {
     if (broken) *out = INFINITY;
     return SOS_OK;
   };
-  double best = INFINITY;
+  // The on-chip form is kept apart: the others go on to team sizes of their own
+  // for each bucket, which may beat it where the uniform ones do not (40
+  // subdomains of 16 x 2 x 2 to 8 elements: 0.286 ms on the chip, 0.265 in teams of 8, 2, 2).
+  double best = INFINITY, chip_best = INFINITY;
+  int chip_team = 1;
   Shape bs{c->fused_threads, c->fused_cpt, c->fused_ra, c->fused_res};
   std::vector<int32_t> bteams(c->n_buckets, c->fused_team);
   int rc = SOS_OK;
@@ -1264,18 +1301,22 @@ int autotune(sos_ctx* c) {
       ChipPlan plan;
       if (cd.res == 3) {
         if (!chip_plan(c, team, &plan)) continue;
-        chip_shape(c);
-        if (set_team(c, team) != SOS_OK) continue;
+        chip_shape(c, team);
       } else {
-        // (teams of three and six: the on-chip form only, whose blocks hold
-        // a third of 33 planes)
-        if ((team == 3 || team == 6) && !c->opts.team) continue;
+        // (the other team sizes: the on-chip form only, whose blocks hold few
+        // planes)
+        if (!c->opts.team && team != 1 && team != 2 && team != 4 && team != 8) continue;
         if (fused_shape(c, cd.threads, cd.cpt, cd.ra, cd.res) != SOS_OK || set_team(c, team) != SOS_OK) continue;
         if (cd.res && !fused_args(c).res) continue;  // p and x do not fit in LDS with this team
       }
       double ms = INFINITY;
       if ((rc = time_config(&ms))) break;
-      if (ms < best * kTuneMargin) {
+      if (cd.res == 3) {
+        if (ms < chip_best * kTuneMargin) {
+          chip_best = ms;
+          chip_team = team;
+        }
+      } else if (ms < best * kTuneMargin) {
         best = ms;
         bs = cd;
         bteams.assign(c->n_buckets, team);
@@ -1284,7 +1325,7 @@ int autotune(sos_ctx* c) {
   // per-bucket team sizes with the best shape: two passes of coordinate
   // descent, smallest bucket first (shrinking the small subdomains' teams
   // frees co-resident blocks that the large ones' teams then need)
-  if (!rc && c->n_buckets > 1 && !c->opts.team && std::isfinite(best) && bs.res != 3 &&
+  if (!rc && c->n_buckets > 1 && !c->opts.team && std::isfinite(best) &&
       fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res) == SOS_OK) {
     for (int pass = 0; pass < 2 * c->n_buckets && !rc; ++pass) {
       const int b = c->n_buckets - 1 - pass % c->n_buckets;
@@ -1308,13 +1349,15 @@ int autotune(sos_ctx* c) {
   if (rc) return rc;
   HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (bs.res == 3) {
-    chip_shape(c);
-    bs.threads = 0;
+  if (std::isfinite(chip_best) && !(best < chip_best * kTuneMargin)) {
+    best = chip_best;
+    bs = {0, 2, 1, 3};
+    bteams.assign(c->n_buckets, chip_team);
+    chip_shape(c, chip_team);
   } else {
     rc = fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res);
+    if (!rc) rc = set_bucket_teams(c, bteams);
   }
-  if (!rc) rc = set_bucket_teams(c, bteams);
   if (rc) return rc;
   c->tune_ms = best;
   invalidate_graph(c);
@@ -1709,16 +1752,17 @@ int sos_teams(const sos_ctx* c, int32_t* teams) {
 
 int sos_set_teams(sos_ctx* c, const int32_t* teams) {
   if (!c || !teams) return fail(SOS_EINVAL, "NULL argument");
-  int rc = set_teams(c, std::vector<int32_t>(teams, teams + c->subs.size()));
-  if (rc) return rc;
-  // the on-chip form takes one team size for all subdomains
-  if (c->fused_res == 3) {
-    ChipPlan plan;
-    bool same = true;
-    for (int32_t t : c->sub_team) same = same && t == c->sub_team[0];
-    if ((!same || !chip_plan(c, c->fused_team, &plan)) &&
-        (rc = fused_shape(c, c->opts.block, 0, c->opts.wave_rows, c->opts.resident)))
-      return rc;
+  const std::vector<int32_t> t(teams, teams + c->subs.size());
+  // the on-chip form takes one team size for all subdomains, and alone one of
+  // more than kMaxTeam (such as another context's sos_teams)
+  ChipPlan plan;
+  const bool same = std::count(t.begin(), t.end(), t[0]) == (ptrdiff_t)t.size();
+  if ((c->fused_res == 3 || t[0] > kMaxTeam) && same && chip_plan(c, t[0], &plan)) {
+    chip_shape(c, t[0]);
+  } else {
+    if (int rc = set_teams(c, t)) return rc;
+    if (c->fused_res == 3)
+      if (int rc = fused_shape(c, c->opts.block, 0, c->opts.wave_rows, c->opts.resident)) return rc;
   }
   c->tuned = true;  // keep these teams and the current block shape
   return SOS_OK;

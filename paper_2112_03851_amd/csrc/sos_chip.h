@@ -154,10 +154,15 @@ struct ChipRed {
   int job;
 };
 
+// Partial sums of subdomain s: [member][parity][kTeamSlot], TM members.
+__device__ __forceinline__ double* chip_part(const FusedArgs& a, int s) {
+  return a.team_part + (size_t)s * a.team * 2 * kTeamSlot;
+}
+
 template <int N, class F>
 __device__ __forceinline__ void chip_sum(double (&v)[N], ChipRed& sh, const FusedArgs& a, int s, int tau, int TM,
                                          int epoch, unsigned long long ticks, int& fail, F&& meanwhile) {
-  static_assert(N <= kChipSums && kMaxTeam <= 16, "a row of lanes per sum");
+  static_assert(N <= kChipSums, "a row of lanes per sum");
   // (opaque, so that no address below is kept in registers through the sweep)
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
@@ -171,29 +176,29 @@ __device__ __forceinline__ void chip_sum(double (&v)[N], ChipRed& sh, const Fuse
   if (tid == 0) sh.fail = 0;
   __syncthreads();
   if (w == nw - 1) {
-    // row n of the lanes adds the waves' parts of sum n, then the members'
+    // row n of the lanes adds the waves' parts of sum n, then the members',
+    // sixteen at a time
     const int n = lane >> 4, m = lane & 15;
     double part = row_sum15(n < N && m < nw ? sh.wave[n * 16 + m] : 0.0);
     if (TM > 1) {
-      double* const base = a.team_part + (size_t)s * kMaxTeam * 2 * kTeamSlot + (epoch & 1) * kTeamSlot + n;
+      double* const base = chip_part(a, s) + (epoch & 1) * kTeamSlot + n;
       const unsigned tag = (unsigned)((epoch + 1) & 0xFF);
       const unsigned want = (unsigned)((epoch + 1 + a.tag_skew) & 0xFF);
       if (n < N && m == 15) st_coh(base + (size_t)tau * 2 * kTeamSlot, with_tag(part, tag));
       part = 0.0;
-      if (n < N && m < TM) {
-        const double* q = base + (size_t)m * 2 * kTeamSlot;
+      const unsigned long long t0 = wall_clock64();
+      for (int mm = m; mm < TM; mm += 16) {
+        if (n >= N) break;
+        const double* q = base + (size_t)mm * 2 * kTeamSlot;
         double val = ld_coh(q);
-        const unsigned long long t0 = wall_clock64();
-        int f = 0;
         while (tag_of(val) != want) {
           if (wall_clock64() - t0 > ticks) {
-            f = 1;
+            sh.fail = 1;
             break;
           }
           val = ld_coh(q);
         }
-        part = with_tag(val, 0u);
-        if (f) sh.fail = 1;
+        part += with_tag(val, 0u);
       }
       part = row_sum15(part);
     }
@@ -793,7 +798,7 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
       sh.job = atomicAdd(&a.queue[1], 1) + a.n_teams;
       if (TM > 1) {
         unsigned long long* w = reinterpret_cast<unsigned long long*>(
-            a.team_part + (size_t)s * kMaxTeam * 2 * kTeamSlot + kTeamSlot - 1);
+            chip_part(a, s) + kTeamSlot - 1);
         st_coh(w, (unsigned long long)sh.job + 1ull);
       }
     }
@@ -826,7 +831,7 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
     }
     if (tid == 0 && tau != 0) {
       const unsigned long long* w = reinterpret_cast<const unsigned long long*>(
-          a.team_part + (size_t)s * kMaxTeam * 2 * kTeamSlot + kTeamSlot - 1);
+          chip_part(a, s) + kTeamSlot - 1);
       const unsigned long long t0 = wall_clock64();
       unsigned long long v = ld_coh(w);
       while (v == 0ull && wall_clock64() - t0 <= ticks) v = ld_coh(w);

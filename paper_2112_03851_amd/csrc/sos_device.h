@@ -772,7 +772,7 @@ __global__ void __launch_bounds__(Bound<CPT>::value) k_residual(Dev d, const Blo
                                                    const double* __restrict__ f, const double* __restrict__ lam,
                                                    double* __restrict__ b, double* __restrict__ bx,
                                                    TO* __restrict__ r, double* __restrict__ part,
-                                                   double* __restrict__ team_part, int32_t* __restrict__ queue) {
+                                                   double* __restrict__ team_part, int team_words, int32_t* __restrict__ queue) {
   extern __shared__ __align__(16) unsigned char smem[];
   double* lds = reinterpret_cast<double*>(smem);
   const BlockDesc bd = blocks[blockIdx.x];
@@ -780,8 +780,7 @@ __global__ void __launch_bounds__(Bound<CPT>::value) k_residual(Dev d, const Blo
   // every slot (tag 0), each subdomain's by its first block (one block for
   // all of them was the launch's longest), and the on-chip form's counters
   if (team_part && bd.z0 == 0)
-    for (int i = threadIdx.x; i < kMaxTeam * 2 * 4; i += blockDim.x)
-      team_part[(size_t)bd.s * (kMaxTeam * 2 * 4) + i] = 0.0;
+    for (int i = threadIdx.x; i < team_words; i += blockDim.x) team_part[(size_t)bd.s * team_words + i] = 0.0;
   if (queue && blockIdx.x == 0 && threadIdx.x < 3) queue[threadIdx.x] = threadIdx.x == 2 ? queue[2] + 1 : 0;
   const SubDesc sd = d.subs[bd.s];
   shell_edges(d, sd, bd.z0, bd.z1, f, lam, b, bx);

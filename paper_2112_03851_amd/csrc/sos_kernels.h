@@ -33,6 +33,7 @@ struct Dev {
 };
 
 constexpr int kMaxTeam = 8;  // blocks per subdomain in the fused kernel
+constexpr int kMaxChipTeam = 64;  // and in its on-chip form
 constexpr int kMinSeg = 8;  // shortest z-segment of a march (planes)
 
 // Number of z-segments a block of `threads` threads with `cpt` x-y columns per
@@ -83,11 +84,11 @@ hipError_t launch_load_nodes(const Dev& d, int max_n, const double* f_nodes, dou
 // b = f), in bx on the x-boundary nodes (SubDesc::xoff) and in b elsewhere;
 // then r = b - A u (FP64 apply), stored as Tr; partials (r'D^-1 r if rz, else
 // 0), r'r, b'b per block. team_part (optional): the fused kernel's team
-// slots, n_sub * kMaxTeam * 8 doubles, and queue (optional): its ticket and
+// slots, team_words doubles per subdomain, and queue (optional): its ticket and
 // job counters, both cleared for the launch that follows, which is counted.
 hipError_t launch_residual(const Dev& d, const SegLaunch& L, int fp32, bool rz, const double* u,
                            const double* f, const double* lam, double* b, double* bx, void* r_out, double* part,
-                           double* team_part, int32_t* queue, hipStream_t st);
+                           double* team_part, int team_words, int32_t* queue, hipStream_t st);
 // Why a subdomain's inner solve stopped early, OR-ed into one device word
 // per solve (the host reads it at every convergence check).
 enum BreakBits : int32_t {
@@ -133,7 +134,7 @@ struct FusedArgs {
   unsigned long long* iters_total;  // [0] CG iterations, [1] algorithmic bytes
   int32_t nblocks;                  // grid size (teams plus idle padding blocks)
   int32_t team;                     // the largest team (1: no inter-block sync anywhere)
-  double* team_part;                // n_sub * kMaxTeam * 2 * 4 tagged partial sums (cleared by
+  double* team_part;                // n_sub * kMaxTeam (on-chip form: team) * 2 * 4 tagged partial sums (cleared by
                                     // the residual kernel before each launch)
   int32_t zu;                       // every block marches one segment (uniform z variant)
   int32_t rows;                     // wave-owned rows (see ra_rows): one barrier per plane
@@ -163,6 +164,7 @@ __host__ __device__ inline size_t chip_lds(int np, int ny, int zlen, size_t es, 
   const size_t n = (size_t)zlen * np * ny;
   return ((wl ? 2 * chip_even(n) : 0) + 4 * n + (size_t)4 * np * (ny + 4)) * es;
 }
+constexpr int kChipPlanes[] = {5, 9, 12, 17};  // most planes per block of the kernel variants
 constexpr int kChipAhead = 2;  // planes of w read ahead from the private buffer
 constexpr int kChipPrivate = 5;  // private 4-value records per thread: r, s of four halo planes, the ends' diagonal
 constexpr size_t kChipStatic = 1024;  // room for its static LDS

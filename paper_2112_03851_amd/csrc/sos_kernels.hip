@@ -624,32 +624,32 @@ hipError_t launch_load_nodes(const Dev& d, int max_n, const double* f_nodes, dou
 
 hipError_t launch_residual(const Dev& d, const SegLaunch& L, int fp32, bool rz, const double* u, const double* f,
                            const double* lam, double* b, double* bx, void* r_out, double* part, double* team_part,
-                           int32_t* queue, hipStream_t st) {
+                           int team_words, int32_t* queue, hipStream_t st) {
   SOS_DISPATCH_Q(d.hasq, {
   if (fp32 && rz && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, true, true>), dim3(L.nblocks),
                                                dim3(L.threads), L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out,
-                                               part, team_part, queue));
+                                               part, team_part, team_words, queue));
   } else if (fp32 && rz) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, true>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part, queue));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part, team_words, queue));
   } else if (fp32 && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, false, true>), dim3(L.nblocks),
                                                dim3(L.threads), L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part,
-                                               team_part, queue));
+                                               team_part, team_words, queue));
   } else if (fp32) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<float, C, Q, false>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part, queue));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (float*)r_out, part, team_part, team_words, queue));
   } else if (rz && L.zu) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<double, C, Q, true, true>), dim3(L.nblocks),
                                                dim3(L.threads), L.lds64, st, d, L.blocks, u, f, lam, b, bx,
-                                               (double*)r_out, part, team_part, queue));
+                                               (double*)r_out, part, team_part, team_words, queue));
   } else if (rz) {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<double, C, Q, true>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part, queue));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part, team_words, queue));
   } else {
     SOS_DISPATCH_CPT(L.cpt, hipLaunchKernelGGL((k_residual<double, C, Q, false>), dim3(L.nblocks), dim3(L.threads),
-                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part, queue));
+                                               L.lds64, st, d, L.blocks, u, f, lam, b, bx, (double*)r_out, part, team_part, team_words, queue));
   }
   });
   return hipGetLastError();

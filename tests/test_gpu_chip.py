@@ -90,6 +90,9 @@ SOLVES = {
     "plane33_5_planes": (dict(ne=(48, 48, 20), cuts=((16, 32), (16, 32), ()), p=16.0), "fp32", 8),
     "plane33_fp64": (dict(ne=(48, 48, 20), cuts=((16, 32), (16, 32), ()), p=16.0), "fp64", 8),
     "plane21_17_planes": (dict(ne=(20, 20, 17), cuts=((10,), (10,), ()), p=16.0), "fp32", 2),
+    "team16_3_planes": (dict(ne=(32, 32, 24), cuts=((16,), (16,), ()), p=16.0), "fp32", 16),
+    "team48_slab": (dict(ne=(20, 18, 52), lengths=(1.0, 1.0, 3.0), cuts=((5, 10, 15), (), ()), p=20.0), "fp32", 48),
+    "team24_fp64": (dict(ne=(20, 18, 52), lengths=(1.0, 1.0, 3.0), cuts=((5, 10, 15), (), ()), p=20.0), "fp64", 24),
     "many_teams": (dict(ne=(60, 60, 12), cuts=(tuple(range(5, 60, 5)), tuple(range(5, 60, 5)), (3, 6, 9)), p=24.0),
                    "fp32", 3),
 }
@@ -141,3 +144,26 @@ def test_unequal_teams_leave_the_chip_form(tmp_path, monkeypatch):
     phi, st = prob.solve(d, 1e-8)
     assert st["converged"]
     prob.close()
+
+
+def test_teams_of_another_context(tmp_path, monkeypatch):
+    """Teams of more than eight members, as one context reports them, are taken
+    by a fresh one; unequal ones of that size are refused."""
+    import torch
+    from paper_2112_03851_amd.sos import SosError
+    kw, prec, team = SOLVES["team48_slab"]
+    case = Case(**kw)
+    opts = dict(precision=prec, mode="batched", check_every=10, max_outer=20000, inner_tol=1e-2, inner_abs=0.0)
+    prob, d = _forced(case, team, tmp_path, monkeypatch, **opts)
+    phi, st = prob.solve(d, 1e-8)
+    teams = prob.teams()
+    prob.close()
+    other = case.problem(**opts)
+    bad = np.array(teams)
+    bad[0] = 9
+    with pytest.raises(SosError):
+        other.set_teams(bad)
+    other.set_teams(teams)
+    phi2, st2 = other.solve(d, 1e-8)
+    assert st["team"] == st2["team"] == team and st2["resident"] == 3 and torch.equal(phi, phi2)
+    other.close()

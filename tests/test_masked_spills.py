@@ -33,6 +33,8 @@ def test_spill_before_the_mask_is_restored_is_found():
     assert masked_spills(LOOP % (SPILL, "")) == [("_Z3foo", "scratch_store_dword off, v38, off offset:24")]
     assert masked_spills(LOOP % ("\tv_mov_b32_e32 v1, v2\n", "")) == [("_Z3foo", "v_mov_b32_e32 v1, v2")]
     assert masked_spills(LOOP % ("", SPILL)) == []
+    exit_only = (LOOP % (SPILL, "")).replace(".LBB0_3:", "; %bb.3:")
+    assert masked_spills(exit_only) == [("_Z3foo", "scratch_store_dword off, v38, off offset:24")]
 
 
 @pytest.mark.gpu

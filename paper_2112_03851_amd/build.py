@@ -24,7 +24,7 @@ ARCH = "gfx950"
 UNITS = [("sos_kernels.hip", [], "sos_kernels.o"),
          ("sos_api.hip", [], "sos_api.o"),
          ("sos_cmaes.cpp", [], "sos_cmaes.o")] + \
-        [("sos_fused.hip", [f"-DSOS_FUSED_CPT={c}"], f"sos_fused_c{c}.o") for c in (1, 2, 3, 4)] + \
+        [("sos_fused.hip", [f"-DSOS_FUSED_CPT={c}", "-DSOS_CHIP_APART"], f"sos_fused_c{c}.o") for c in (1, 2, 3, 4)] + \
         [("sos_chip.hip", [f"-DSOS_CHIP_SET={k}"], f"sos_chip_{k}.o") for k in (0, 1, 2, 3, 4, 5)]
 
 

@@ -1,17 +1,13 @@
 // Launches of the on-chip fused CG kernel (sos_chip.h) for one set of
 // variants, SOS_CHIP_SET (compiled once per value), and their dispatch
-// (SOS_CHIP_SET 0).
+// (SOS_CHIP_SET 0); all sets in one unit with SOS_CHIP_SET -1.
 #include "sos_chip.h"
 
 #ifndef SOS_CHIP_SET
-#error SOS_CHIP_SET must be defined (0..5)
+#error SOS_CHIP_SET must be defined (0..5, or -1)
 #endif
 
 namespace sos {
-
-template <int SET>
-hipError_t launch_chip_set(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
-                           int* per_cu);
 
 template <typename T, int P, int NP, bool Q, bool WL>
 static hipError_t chip_one(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
@@ -37,35 +33,35 @@ static hipError_t chip_np(const Dev& d, const SegLaunch& L, int threads, const F
   return hipErrorInvalidValue;
 }
 
-template <>
-hipError_t launch_chip_set<SOS_CHIP_SET>(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a,
-                                         hipStream_t st, int* per_cu) {
-#if SOS_CHIP_SET == 0
-  return chip_np<float, 17, false>(d, L, threads, a, st, per_cu);
-#elif SOS_CHIP_SET == 1
-  return chip_np<float, 17, true>(d, L, threads, a, st, per_cu);
-#elif SOS_CHIP_SET == 2
-  return chip_np<float, 9, true>(d, L, threads, a, st, per_cu);
-#elif SOS_CHIP_SET == 5
-  return chip_np<float, 12, true>(d, L, threads, a, st, per_cu);
-#elif SOS_CHIP_SET == 3
-  return chip_np<float, 5, true>(d, L, threads, a, st, per_cu);
-#else
-  return chip_np<double, 5, true>(d, L, threads, a, st, per_cu);
-#endif
+// One set of variants (each set compiled in a translation unit of its own).
+template <int SET>
+hipError_t launch_chip_set(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
+                           int* per_cu) {
+  if constexpr (SET == 0) return chip_np<float, 17, false>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 1) return chip_np<float, 17, true>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 2) return chip_np<float, 9, true>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 3) return chip_np<float, 5, true>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 4) return chip_np<double, 5, true>(d, L, threads, a, st, per_cu);
+  else return chip_np<float, 12, true>(d, L, threads, a, st, per_cu);
 }
 
+#define SOS_CHIP_DECL(PREFIX, SET)                                                                      \
+  PREFIX template hipError_t launch_chip_set<SET>(const Dev&, const SegLaunch&, int, const FusedArgs&, \
+                                                  hipStream_t, int*);
+
+#if SOS_CHIP_SET > 0
+SOS_CHIP_DECL(, SOS_CHIP_SET)
+#endif
+
+// The first unit also dispatches (the only one with SOS_CHIP_SET -1: all sets).
+#if SOS_CHIP_SET <= 0
 #if SOS_CHIP_SET == 0
-template <>
-hipError_t launch_chip_set<1>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
-template <>
-hipError_t launch_chip_set<2>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
-template <>
-hipError_t launch_chip_set<3>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
-template <>
-hipError_t launch_chip_set<5>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
-template <>
-hipError_t launch_chip_set<4>(const Dev&, const SegLaunch&, int, const FusedArgs&, hipStream_t, int*);
+SOS_CHIP_DECL(extern, 1)
+SOS_CHIP_DECL(extern, 2)
+SOS_CHIP_DECL(extern, 3)
+SOS_CHIP_DECL(extern, 4)
+SOS_CHIP_DECL(extern, 5)
+#endif
 
 hipError_t launch_chip(const Dev& d, const SegLaunch& L, int fp32, int threads, const FusedArgs& a, hipStream_t st,
                        int* per_cu) {

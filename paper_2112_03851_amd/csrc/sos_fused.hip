@@ -90,3 +90,10 @@ template hipError_t launch_fused_cpt<SOS_FUSED_CPT>(const Dev&, const SegLaunch&
                                                     const FusedArgs&, hipStream_t, bool*);
 
 }  // namespace sos
+
+// A build of one unit per number of columns (host code only, under the
+// sanitizers) has the on-chip form's launches here.
+#if SOS_FUSED_CPT == 1 && !defined(SOS_CHIP_APART)
+#define SOS_CHIP_SET -1
+#include "sos_chip.hip"
+#endif

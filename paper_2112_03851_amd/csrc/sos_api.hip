@@ -48,6 +48,7 @@ struct Seg {
   std::vector<int32_t> bfirst;
   BlockDesc* d_blocks = nullptr;
   int32_t* d_bfirst = nullptr;
+  int32_t extra = 0;  // blocks that segments shorter than kMinSeg add
   SegLaunch L{};
 };
 
@@ -57,7 +58,9 @@ struct Seg {
 // address (it is a host-side stand-in there); it uses the device address that
 // hipGetSymbolAddress returns, resolved once per device at set-up.
 constexpr size_t kScratchBytes = size_t(48) << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// (room beyond the limit for the partials of at most 256 blocks that idle compute
+// units add to a small problem, build_seg: they do not count against it)
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + 8192];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -287,13 +290,17 @@ int build_seg(sos_ctx* c) {
   const int spread = 256 / n_sub;
   g.blocks.clear();
   g.bfirst.assign(1, 0);
+  g.extra = 0;
   size_t lds64 = 0, lds32 = 0;
   bool zu = true;
   for (int s = 0; s < n_sub; ++s) {
     const SubDesc& d = c->subs[s];
     const int nz = d.n[2];
-    int chunks = std::max(std::min(want, std::max(1, nz / kMinSeg)), std::min(spread, nz / 2));
-    int len = (nz + chunks - 1) / chunks;
+    const int longer = std::min(want, std::max(1, nz / kMinSeg));
+    const int chunks = std::max(longer, std::min(spread, nz / 2));
+    const int len = (nz + chunks - 1) / chunks;
+    auto blocks_of = [&](int l) { return (nz + l - 1) / l; };
+    g.extra += blocks_of(len) - blocks_of((nz + longer - 1) / longer);
     for (int z = 0; z < nz; z += len) {
       BlockDesc b{s, z, std::min(nz, z + len), g.bfirst.back(), 0, {0, 0, 0}};
       g.blocks.push_back(b);
@@ -1916,7 +1923,8 @@ int sos_residual_noalloc(sos_ctx* c, double* phi, double* res) {
   // ut and rho (local layout), the check partials and the result words
   const size_t n_vec = (size_t)align64(c->n_local);
   const size_t n_part = (size_t)align64(2 * (int64_t)c->n_norm_blocks);
-  const size_t need = (2 * n_vec + n_part + 4 + (size_t)c->geo.copies) * sizeof(double);
+  const size_t n_counted = (size_t)align64(2 * (int64_t)(c->n_norm_blocks - c->seg.extra));
+  const size_t need = (2 * n_vec + n_counted + 4 + (size_t)c->geo.copies) * sizeof(double);
   if (need > kScratchBytes)
     return fail(SOS_EINVAL, "the global residual of %lld local unknowns needs %zu bytes of scratch; the "
                 "allocation-free variant holds at most %zu bytes (about %zu local unknowns)",

@@ -43,7 +43,7 @@ PMC_GLOB = os.path.join(ROOT, "profiles", "fused_cg_*_pmc.json")
 GOLDEN_COUNTS = os.path.join(ROOT, "tests", "golden", "oracle_outer_counts.json")
 CSRC = os.path.join(ROOT, "paper_2112_03851_amd", "csrc")
 KERNEL_SRCS = [os.path.join(CSRC, n) for n in ("sos_device.h", "sos_kernels.h", "sos_internal.h", "sos_kernels.hip",
-                                               "sos_fused.hip")]
+                                               "sos_fused.hip", "sos_chip.h", "sos_chip.hip")]
 
 
 def kernel_sha():
@@ -319,7 +319,7 @@ def main():
     traffic = measured_traffic(launch_bytes, ref, args.workload)
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                "kernel": "k_fused_cg<float>", "avg_launch_ms": launch_s * 1e3,
+                "kernel": "k_chip_cg<float>" if ref["resident"] == 3 else "k_fused_cg<float>", "avg_launch_ms": launch_s * 1e3,
                 "algorithmic_bytes_per_launch": launch_bytes, "launches": ref["kernel_launches"],
                 "basis": "algorithmic bytes (12 FP32 words per CG iteration and local unknown + the FP64 update "
                          "of u, counted by the kernel) / average launch duration from HIP events on the "

@@ -21,7 +21,20 @@
 //
 // What bounds it: the issue of vector instructions (about 90 per pair and
 // plane, three waves per SIMD at 33 x 33 planes) and the latency of a plane's
-// chain, no longer memory.
+// chain, no longer memory. A sweep takes, in cycles of a block at 33 x 33
+// nodes, about 1450 a plane (1830 with every unit busy, 2640 where w is in the
+// private buffer), 2000 to 3000 for each neighbour's two halo planes and 6000 to
+// 9000 for the meeting, most of it two trips between compute units. At 17 x 17
+// nodes in teams of eight a plane takes 980 and a sweep 12000.
+//
+// Whole solves against k_fused_cg, each in its tuned shape: 128^3 elements in
+// 512 subdomains, second-order condition, 1715 -> 980 ms; 96^3 in 216, 1016 ->
+// 914 ms; 64^3 in 64, 772 -> 672 ms; 48^3 in 27, FP64 and adjoint, 878 -> 390 ms.
+// k_fused_cg stays where a plane has few rows and many subdomains fill the chip
+// anyway: a block of six waves leaves no room for a second one on its unit
+// (256 columns of 12 x 12 x 96 nodes: 470 ms there, 690 here; 64 slabs of 11 x 39
+// x 639: 288 against 279 to 330), and where whole subdomains in one block need
+// no team at all (256 of 32^3: 123 against 132 ms).
 #pragma once
 
 #include "sos_device.h"

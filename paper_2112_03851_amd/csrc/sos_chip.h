@@ -38,6 +38,7 @@
 #pragma once
 
 #include "sos_device.h"
+#include "sos_mail.h"
 
 namespace sos {
 
@@ -803,8 +804,8 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
         alpha = uniform(T(dalpha));
         beta = uniform(T(dbeta));
       }
+      seq = mail_next_job(seq);  // (not for a subdomain without a sweep)
     }
-    ++seq;
     // the next subdomain of this team: the first member takes it and leaves it
     // in a spare word of this subdomain's slots for the others
     if (tid == 0 && tau == 0) {

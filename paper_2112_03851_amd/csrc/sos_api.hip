@@ -20,6 +20,7 @@
 #include "../../include/sos.h"
 #include "sos_internal.h"
 #include "sos_kernels.h"
+#include "sos_mail.h"
 
 using namespace sos;
 
@@ -151,7 +152,8 @@ struct sos_ctx {
   ChipPlan chip{};
   void* chip_ws = nullptr;
   size_t chip_bytes = 0;
-  int32_t* queue = nullptr;  // ticket and job counters
+  int32_t* queue = nullptr;  // ticket and job counters, launches since the mailboxes were cleared
+  uint32_t mail_left = 0;    // launches that may follow before they are cleared again
   size_t fused_lds = 0;
   double* team_part = nullptr;   // team partial sums
   bool tuned = false;    // fused block shape chosen (explicit or autotuned)
@@ -544,7 +546,6 @@ int ensure_fmap(sos_ctx* c) {
       c->chip_ws = nullptr;
       c->chip_bytes = 0;
       if (int rc = dalloc_v(&c->chip_ws, need)) return rc;
-      // no word of the mailboxes carries a sequence number yet
       HIPCHK(hipMemsetAsync(c->chip_ws, 0, need, c->stream));
       c->chip_bytes = need;
     }
@@ -876,6 +877,7 @@ FusedArgs fused_args(sos_ctx* c) {
     a.chip_pairs = p.pairs;
     a.chip_wl = p.wl;
     a.chip_slots = p.slots;
+    a.chip_span = mail_span(a.n_jobs, p.n_teams, c->opts.max_inner);
     char* ws = static_cast<char*>(c->chip_ws);
     a.team_part = static_cast<double*>(c->chip_ws);
     ws += p.part;
@@ -932,6 +934,36 @@ int team_words(const sos_ctx* c) { return (c->fused_res == 3 ? c->fused_team : k
 
 // The counters of the on-chip form, which the residual kernel clears (else null).
 int32_t* queue_of(sos_ctx* c) { return c->fused_res == 3 ? c->queue : nullptr; }
+
+// Clears the mailboxes of the on-chip form and the count of its launches (fill
+// kernels: a graph may hold them).
+int clear_mail(sos_ctx* c) {
+  HIPCHK(launch_fill(static_cast<double*>(fused_args(c).chip_mail), (int64_t)(c->chip.mail / sizeof(double)), 0.0,
+                     c->stream));
+  HIPCHK(launch_fill(reinterpret_cast<double*>(c->queue), 2, 0.0, c->stream));
+  return SOS_OK;
+}
+
+// Launches of the fused kernel between two clears of the mailboxes (UINT32_MAX:
+// it has none).
+uint32_t mail_period(sos_ctx* c) {
+  return c->fused_res == 3 && c->chip.mail ? mail_launches(fused_args(c).chip_span) : UINT32_MAX;
+}
+
+// Before k launches of the fused kernel (one graph, or one eager launch): the
+// mailboxes have sequence numbers for them, or are cleared. A run of launches
+// starts with mail_left = 0: what the workspace holds there may be the last
+// run's, under another layout or another span of numbers.
+int mail_room(sos_ctx* c, uint32_t k) {
+  const uint32_t period = mail_period(c);
+  if (period == UINT32_MAX) return SOS_OK;
+  if (c->mail_left < k) {
+    if (int rc = clear_mail(c)) return rc;
+    c->mail_left = period;
+  }
+  c->mail_left -= std::min(c->mail_left, k);  // (a longer graph clears them itself, build_graph)
+  return SOS_OK;
+}
 
 int enqueue_batched_iteration(sos_ctx* c, hipEvent_t ev0, hipEvent_t ev1) {
   hipStream_t st = c->stream;
@@ -998,8 +1030,11 @@ int build_graph(sos_ctx* c, int k) {
   invalidate_graph(c);
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
   int rc = SOS_OK;
-  for (int i = 0; i < k && rc == SOS_OK; ++i)
-    rc = enqueue_batched_iteration(c, nullptr, nullptr);
+  const uint32_t period = mail_period(c);
+  for (int i = 0; i < k && rc == SOS_OK; ++i) {
+    if (i > 0 && (uint32_t)i % period == 0) rc = clear_mail(c);
+    if (rc == SOS_OK) rc = enqueue_batched_iteration(c, nullptr, nullptr);
+  }
   if (rc == SOS_OK) rc = enqueue_check(c, nullptr);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(c->stream, &g);
@@ -1075,6 +1110,7 @@ int run_outer(sos_ctx* c, double tol, int max_outer, sos_stats* stats, bool* con
   if (batched) {
     int rc = ensure_fmap(c);
     if (rc) return rc;
+    c->mail_left = 0;
   }
   // HIP events recorded inside a graph cannot be read back with
   // hipEventElapsedTime: timed runs launch eagerly; so do cooperative team
@@ -1105,6 +1141,10 @@ int run_outer(sos_ctx* c, double tol, int max_outer, sos_stats* stats, bool* con
           return rc;
         }
       }
+      if (int rc = mail_room(c, (uint32_t)k)) {
+        roctxRangePop();
+        return rc;
+      }
       HIPCHK(hipGraphLaunch(c->gexec, st));
     } else {
       for (int i = 0; i < k; ++i) {
@@ -1116,7 +1156,8 @@ int run_outer(sos_ctx* c, double tol, int max_outer, sos_stats* stats, bool* con
             evs.push_back(e0);
             evs.push_back(e1);
           }
-          int rc = enqueue_batched_iteration(c, e0, e1);
+          int rc = mail_room(c, 1);
+          if (!rc) rc = enqueue_batched_iteration(c, e0, e1);
           if (rc) return rc;
         } else {
           int rc = stepwise_iteration(c);
@@ -1272,7 +1313,9 @@ int autotune(sos_ctx* c) {
     int rc = ensure_fmap(c);
     if (rc) return rc;
     HIPCHK(hipMemsetAsync(c->flags, 0, sizeof(int32_t), st));
+    c->mail_left = 0;
     for (int rep = 0; rep < 3; ++rep) {
+      if ((rc = mail_room(c, 1))) return rc;
       HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
       HIPCHK(launch_residual(c->dev, c->seg.L, c->fp32, false, c->u, c->f, c->lam, c->b, c->bxf, c->r, c->part,
                              team_slots(c), team_words(c), queue_of(c), st));
@@ -1651,7 +1694,7 @@ int sos_setup_batch(const sos_mesh* mesh, const sos_partition* part, int32_t cop
       (rc = dalloc_v(&c->s1, c->n_local * es)) || (rc = dalloc(&c->part, 3 * c->seg.blocks.size())) ||
       (rc = dalloc(&c->part_norm, 2 * (size_t)c->n_norm_blocks)) || (rc = dalloc(&c->d_res, 4 + (size_t)copies)) ||
       (rc = dalloc(&c->scal, c->subs.size())) || (rc = dalloc(&c->ndone, 1)) || (rc = dalloc(&c->counters, 2)) ||
-      (rc = dalloc(&c->flags, 1)) || (rc = dalloc(&c->queue, 3)) ||
+      (rc = dalloc(&c->flags, 1)) || (rc = dalloc(&c->queue, 4)) ||
       (rc = dalloc(&c->team_part, c->subs.size() * kMaxTeam * 2 * 4))) {
     release(c);
     return rc;
@@ -1697,7 +1740,7 @@ int sos_setup_batch(const sos_mesh* mesh, const sos_partition* part, int32_t cop
   if (e == hipSuccess) e = hipMemset(c->lam, 0, std::max<int64_t>(1, c->n_lam) * sizeof(double));
   if (e == hipSuccess) e = hipMemset(c->rho, 0, c->n_local * sizeof(double));
   if (e == hipSuccess) e = hipMemset(c->flags, 0, sizeof(int32_t));
-  if (e == hipSuccess) e = hipMemset(c->queue, 0, 3 * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMemset(c->queue, 0, 4 * sizeof(int32_t));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     release(c);

@@ -254,10 +254,9 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
   const int team = uniform(ticket / TM), tau = ticket - team * TM;
   if (team >= a.n_teams) return;  // (the host launches n_teams teams)
   int job = team;
-  // sequence number of this launch's sweeps (the launch count in the upper
-  // bits): the same in every member, another in every sweep that may have left
-  // its edge planes in the same place
-  unsigned seq = (unsigned)uniform(a.queue[2]) << 20;
+  // sequence number of the sweep: the same in every member, another in every
+  // sweep since the mailboxes were cleared
+  unsigned seq = mail_first((unsigned)uniform(a.queue[2]), a.chip_span);
   unsigned long long ticks = a.spin_ticks * 64ull;  // the first meeting: a member may still wait for a place
   while (job < a.n_jobs) {
     const int s = uniform(a.fmap[job].s);

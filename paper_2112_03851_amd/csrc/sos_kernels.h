@@ -143,11 +143,13 @@ struct FusedArgs {
   int32_t* flags;                   // BreakBits of the solve, OR-ed by every block that stops early
   uint64_t spin_ticks;              // team barrier: longest wait (wall clock ticks, 100 MHz)
   // on-chip form (res == 3, sos_chip.h)
-  int32_t* queue;                   // [0] block tickets, [1] jobs taken (cleared by the residual kernel), [2] launches (it counts)
+  int32_t* queue;                   // [0] block tickets, [1] jobs taken (cleared by the residual kernel), [2] launches since the
+                                    // mailboxes were cleared (it counts)
   int32_t n_jobs, n_teams;          // subdomains, teams of the grid
   int32_t chip_planes, chip_pairs;  // kernel variant: planes per block, pairs per row (0: any)
   int32_t chip_wl;                  // kernel variant: w in LDS
   int32_t chip_slots;               // most pairs of a plane of any subdomain
+  uint32_t chip_span;               // sequence numbers of a launch (sos_mail.h)
   void *chip_w, *chip_x, *chip_halo, *chip_mail;  // private w, x, halo r and s, exchanged edge planes
   int32_t tag_skew;                 // team barrier: 0; 1 waits for a tag no member writes, so
                                     // every wait ends at spin_ticks (failure-handling tests)

@@ -144,7 +144,13 @@ struct Model {
 }  // namespace
 
 // members counts_skipped first sweeps...
+// numbers jobs teams max_inner launch: span, launches between two clears, first number of the launch
 int main(int argc, char** argv) {
+  if (argc == 6 && !strcmp(argv[1], "numbers")) {
+    const uint32_t span = sos::mail_span(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]));
+    printf("%u %u %u\n", span, sos::mail_launches(span), sos::mail_first((uint32_t)strtoul(argv[5], nullptr, 10), span));
+    return 0;
+  }
   if (argc < 5) return 2;
   Model m{atoi(argv[1]), {}, atoi(argv[2]) != 0, (uint32_t)strtoul(argv[3], nullptr, 10)};
   for (int i = 4; i < argc; ++i) m.jobs.push_back(atoi(argv[i]));

@@ -763,8 +763,42 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
             mail_write(m + (size_t)((e4 < 2 ? e4 : e4 + 2) * cs) * MW, seq, v.a, v.b);
           }
         }
-        if (!live) ag = ad = ar = T(0);
-        double acc[3] = {double(ag), double(ad), double(ar)};
+        double g0 = double(ag), d0 = double(ad);
+        if constexpr (sizeof(T) < sizeof(double)) {
+          // every step length and direction of the solve descends from the first
+          // gamma and delta: FP64 products and sums, as in k_fused_cg (the sums of the
+          // later sweeps are the inner precision's within a thread there too)
+          if (n == 0) {
+            g0 = d0 = 0.0;
+            uint32_t qw = lds0 + (uint32_t)slot * (uint32_t)sizeof(P2<T>), gw = (uint32_t)tid * (uint32_t)sizeof(P2<T>);
+            int k = zb0 + zk, more = zlen;
+            asm volatile("" : "+v"(qw), "+v"(gw), "+v"(k), "+v"(more));
+            k = uniform(k);
+            more = uniform(more);
+            unroll<0, P>([&](auto ic) {
+              constexpr int i = decltype(ic)::value;
+              if (more > 0) {
+                T da, db;
+                dinv(k, da, db);
+                P2<T> w;
+                if constexpr (WL) w = lds_at<P2<T>>(qw);
+                else w = *reinterpret_cast<const P2<T>*>(reinterpret_cast<const char*>(wg) + gw);
+                const T ua = da * ra[i], ub = db * rb[i];
+                g0 += double(ra[i]) * double(ua);
+                g0 += double(rb[i]) * double(ub);
+                d0 += double(w.a) * double(ua);
+                d0 += double(w.b) * double(ub);
+                if constexpr (WL) qw += plane;
+                else gw += (uint32_t)nthreads * (uint32_t)sizeof(P2<T>);
+                asm("" : "+v"(qw), "+v"(gw));
+                k = scalar_add<1>(k);
+                more = scalar_add<-1>(more);
+              }
+            });
+          }
+        }
+        if (!live) g0 = d0 = 0.0, ar = T(0);
+        double acc[3] = {g0, d0, double(ar)};
         chip_sum(acc, sh, a, s, tau, TM, epoch++, ticks, tfail, fetch_mail);
         ticks = a.spin_ticks;
         if (tfail) {

@@ -251,7 +251,8 @@ int sos_axes(const sos_ctx* ctx, int32_t* perm);
  * the whole state on the chip one size of up to 64 for all. */
 int sos_teams(const sos_ctx* ctx, int32_t* teams);
 /* Set them (1..8, at most the subdomain's z-planes, or one larger size for all
- * that the form with the whole state on the chip takes; SOS_EINVAL otherwise):
+ * that the form with the whole state on the chip takes; SOS_EINVAL otherwise,
+ * SOS_ENOMEM if there is no memory for that form's workspace):
  * the current block shape and these teams are used from now on without
  * autotuning, until sos_set_opts changes a launch option. */
 int sos_set_teams(sos_ctx* ctx, const int32_t* teams);
@@ -364,6 +365,10 @@ int sos_inner_iters(sos_ctx* ctx, int32_t cap, int32_t* n, int32_t* iters);
  * ends at that bound and the solve reports SOS_EBREAKDOWN (every kernel still
  * exits normally). tag_skew = 0 is normal operation. */
 int sos_debug_barrier(sos_ctx* ctx, int64_t spin_ticks, int32_t tag_skew);
+/* Failure-handling tests: a workspace of more than `bytes` for the form with the
+ * whole state on the chip counts as a failed allocation (0: no limit, the
+ * default). Runs then take the streaming form of the kernel, which needs none. */
+int sos_debug_workspace(sos_ctx* ctx, int64_t bytes);
 
 void sos_destroy(sos_ctx* ctx);
 const char* sos_last_error(void);

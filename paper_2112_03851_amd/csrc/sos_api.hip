@@ -152,6 +152,7 @@ struct sos_ctx {
   ChipPlan chip{};
   void* chip_ws = nullptr;
   size_t chip_bytes = 0;
+  size_t chip_limit = SIZE_MAX;  // a larger workspace counts as a failed allocation (sos_debug_workspace)
   int32_t* queue = nullptr;  // ticket and job counters, launches since the mailboxes were cleared
   uint32_t mail_left = 0;    // launches that may follow before they are cleared again
   size_t fused_lds = 0;
@@ -401,20 +402,25 @@ bool fused_one_segment(const sos_ctx* c) {
   return true;
 }
 
-// Team sizes per subdomain (every copy of a subdomain gets the same).
-int set_teams(sos_ctx* c, const std::vector<int32_t>& teams) {
+// Team sizes per subdomain of the streaming form; the context is unchanged on
+// error.
+int check_teams(const sos_ctx* c, const std::vector<int32_t>& teams) {
   if (teams.size() != c->subs.size()) return fail(SOS_EINVAL, "one team size per subdomain expected");
-  int mx = 1;
   for (size_t i = 0; i < teams.size(); ++i) {
     const int t = teams[i];
     if (t < 1 || t > kMaxTeam) return fail(SOS_EINVAL, "team must be in [1, %d]", kMaxTeam);
     if (c->subs[i].n[2] < t)
       return fail(SOS_EINVAL, "team of %d blocks exceeds subdomain %zu's %d z-planes (marched planes)", t, i,
                   c->subs[i].n[2]);
-    mx = std::max(mx, t);
   }
+  return SOS_OK;
+}
+
+// Sets them (every copy of a subdomain gets the same).
+int set_teams(sos_ctx* c, const std::vector<int32_t>& teams) {
+  if (int rc = check_teams(c, teams)) return rc;
   c->sub_team = teams;
-  c->fused_team = mx;
+  c->fused_team = *std::max_element(teams.begin(), teams.end());
   c->fmap_dirty = true;
   invalidate_graph(c);
   return SOS_OK;
@@ -524,6 +530,36 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   return true;
 }
 
+// The on-chip form's workspace holds the plan's (SOS_ENOMEM where there is no
+// memory for it: the streaming form needs none, so the callers take that then).
+int chip_reserve(sos_ctx* c, const ChipPlan& p) {
+  const size_t need = p.part + p.w + p.x + p.halo + p.mail;
+  if (need > c->chip_limit) return fail(SOS_ENOMEM, "workspace of %zu bytes beyond the limit set", need);
+  if (need <= c->chip_bytes) return SOS_OK;
+  HIPCHK(hipStreamSynchronize(c->stream));
+  invalidate_graph(c);
+  c->fmap_dirty = true;
+  if (c->chip_ws) (void)hipFree(c->chip_ws);
+  c->chip_ws = nullptr;
+  c->chip_bytes = 0;
+  if (int rc = dalloc_v(&c->chip_ws, need)) {
+    (void)hipGetLastError();  // (not for the next launch's check to report)
+    return rc;
+  }
+  HIPCHK(hipMemsetAsync(c->chip_ws, 0, need, c->stream));
+  c->chip_bytes = need;
+  return SOS_OK;
+}
+
+// Back from the on-chip form to the streaming one as set-up leaves it (the
+// default shape where opts.block does not fit).
+int chip_leave(sos_ctx* c) {
+  const sos_opts& o = c->opts;
+  if (fused_shape(c, o.block, 0, o.wave_rows, o.resident) != SOS_OK)
+    if (int rc = fused_shape(c, 0, 0, 0, o.resident)) return rc;
+  return set_team(c, o.team ? o.team : 1);
+}
+
 // The fused kernel's block table: teams in the order of c->order (largest
 // subdomain first). With a team of two or more blocks anywhere, the members of
 // every team share blockIdx % 8 (one XCD under round-robin dispatch, so their
@@ -539,16 +575,7 @@ int ensure_fmap(sos_ctx* c) {
     // one entry per subdomain: the order in which the teams take them
     if (!chip_plan(c, c->fused_team, &c->chip)) return fail(SOS_EINVAL, "the on-chip fused kernel does not fit team %d", c->fused_team);
     c->fused_threads = c->chip.threads;
-    const size_t need = c->chip.part + c->chip.w + c->chip.x + c->chip.halo + c->chip.mail;
-    if (need > c->chip_bytes) {
-      HIPCHK(hipStreamSynchronize(c->stream));
-      if (c->chip_ws) (void)hipFree(c->chip_ws);
-      c->chip_ws = nullptr;
-      c->chip_bytes = 0;
-      if (int rc = dalloc_v(&c->chip_ws, need)) return rc;
-      HIPCHK(hipMemsetAsync(c->chip_ws, 0, need, c->stream));
-      c->chip_bytes = need;
-    }
+    if (int rc = chip_reserve(c, c->chip)) return rc;
   }
   if (chip || c->fused_team <= 1) {
     for (int32_t s : c->order) m.push_back({s, 0, 1, 0});
@@ -1109,6 +1136,10 @@ int run_outer(sos_ctx* c, double tol, int max_outer, sos_stats* stats, bool* con
   const bool log = log_checks();
   if (batched) {
     int rc = ensure_fmap(c);
+    if (rc && c->fused_res == 3) {  // no memory for its workspace
+      c->tuned = false;
+      if (!(rc = chip_leave(c))) rc = ensure_fmap(c);
+    }
     if (rc) return rc;
     c->mail_left = 0;
   }
@@ -1253,7 +1284,11 @@ constexpr double kTuneMargin = 0.99;
 // bucket first, two passes) with the others fixed. The result is cached per (arch,
 // subdomain geometry, precision, inner tolerance).
 int autotune(sos_ctx* c) {
-  if (c->tuned) return SOS_OK;
+  if (c->tuned) {
+    // (the on-chip form with another condition may have another plan)
+    if (c->fused_res != 3 || ensure_fmap(c) == SOS_OK) return SOS_OK;
+    if (int rc = chip_leave(c)) return rc;
+  }
   c->tuned = true;
   const std::string key = tune_key(c);
   // a block shape or team size fixed by the caller is kept: such a partial
@@ -1267,7 +1302,8 @@ int autotune(sos_ctx* c) {
       if (std::count(bt.begin(), bt.end(), bt[0]) == (ptrdiff_t)bt.size() && chip_plan(c, bt[0], &plan) &&
           (!c->opts.team || bt[0] == c->opts.team)) {
         chip_shape(c, bt[0]);
-        return SOS_OK;
+        if (ensure_fmap(c) == SOS_OK) return SOS_OK;
+        if (int rc = chip_leave(c)) return rc;
       }
     } else if (fused_shape(c, th, cp, ra, res && c->opts.resident) == SOS_OK && set_bucket_teams(c, bt) == SOS_OK) {
       return SOS_OK;
@@ -1300,6 +1336,7 @@ int autotune(sos_ctx* c) {
       if (t >= 1 && t <= kMaxChipTeam && team_ok(t, -1)) teams.push_back(t);
   }
   hipStream_t st = c->stream;
+  bool no_memory = false;  // a candidate dropped for want of memory: the result is not the geometry's
   if (int rc0 = zero_directions(c)) return rc0;
   // the trial launches solve the first outer iteration's problem: the
   // right-hand side on the boundary shell as a run starts it
@@ -1311,6 +1348,10 @@ int autotune(sos_ctx* c) {
   auto time_config = [&](double* out) -> int {
     *out = INFINITY;
     int rc = ensure_fmap(c);
+    if (rc == SOS_ENOMEM && c->fused_res == 3) {
+      no_memory = true;
+      return SOS_OK;
+    }
     if (rc) return rc;
     HIPCHK(hipMemsetAsync(c->flags, 0, sizeof(int32_t), st));
     c->mail_left = 0;
@@ -1346,8 +1387,9 @@ int autotune(sos_ctx* c) {
   Shape bs{c->fused_threads, c->fused_cpt, c->fused_ra, c->fused_res};
   std::vector<int32_t> bteams(c->n_buckets, c->fused_team);
   int rc = SOS_OK;
-  for (int team : teams)
+  for (size_t i = 0; i < teams.size() && !rc; ++i)
     for (auto& cd : shapes) {
+      const int team = teams[i];
       ChipPlan plan;
       if (cd.res == 3) {
         if (!chip_plan(c, team, &plan)) continue;
@@ -1399,7 +1441,11 @@ int autotune(sos_ctx* c) {
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (rc) return rc;
+  if (rc) {  // the next solve tunes again
+    c->tuned = false;
+    if (c->fused_res == 3) (void)chip_leave(c);
+    return rc;
+  }
   HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
   HIPCHK(hipStreamSynchronize(st));
   if (std::isfinite(chip_best) && !(best < chip_best * kTuneMargin)) {
@@ -1410,13 +1456,16 @@ int autotune(sos_ctx* c) {
   } else {
     rc = fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res);
     if (!rc) rc = set_bucket_teams(c, bteams);
+    if (c->chip_ws) (void)hipFree(c->chip_ws);  // (the stream is idle)
+    c->chip_ws = nullptr;
+    c->chip_bytes = 0;
   }
   if (rc) return rc;
   c->tune_ms = best;
   invalidate_graph(c);
   // every candidate broke down (a load that is not finite): nothing was learned
   if (!std::isfinite(best)) c->tuned = false;
-  else if (!partial) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best);
+  else if (!partial && !no_memory) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best);
   return SOS_OK;
 }
 
@@ -1810,12 +1859,19 @@ int sos_set_teams(sos_ctx* c, const int32_t* teams) {
   // more than kMaxTeam (such as another context's sos_teams)
   ChipPlan plan;
   const bool same = std::count(t.begin(), t.end(), t[0]) == (ptrdiff_t)t.size();
-  if ((c->fused_res == 3 || t[0] > kMaxTeam) && same && chip_plan(c, t[0], &plan)) {
+  bool chip = (c->fused_res == 3 || t[0] > kMaxTeam) && same && chip_plan(c, t[0], &plan);
+  if (chip)
+    if (int rc = chip_reserve(c, plan)) {
+      if (t[0] > kMaxTeam) return rc;
+      chip = false;
+    }
+  if (chip) {
     chip_shape(c, t[0]);
   } else {
-    if (int rc = set_teams(c, t)) return rc;
+    if (int rc = check_teams(c, t)) return rc;
     if (c->fused_res == 3)
-      if (int rc = fused_shape(c, c->opts.block, 0, c->opts.wave_rows, c->opts.resident)) return rc;
+      if (int rc = chip_leave(c)) return rc;
+    if (int rc = set_teams(c, t)) return rc;
   }
   c->tuned = true;  // keep these teams and the current block shape
   return SOS_OK;
@@ -2036,6 +2092,14 @@ int sos_debug_barrier(sos_ctx* c, int64_t spin_ticks, int32_t tag_skew) {
   c->spin_ticks = spin_ticks ? (uint64_t)spin_ticks : (1ull << 27);
   c->tag_skew = tag_skew;
   invalidate_graph(c);
+  return SOS_OK;
+}
+
+int sos_debug_workspace(sos_ctx* c, int64_t bytes) {
+  if (!c) return fail(SOS_EINVAL, "ctx is NULL");
+  if (bytes < 0) return fail(SOS_EINVAL, "bytes must be >= 0");
+  c->chip_limit = bytes ? (size_t)bytes : SIZE_MAX;
+  c->fmap_dirty = true;
   return SOS_OK;
 }
 

@@ -129,6 +129,7 @@ def lib():
         "sos_set_teams": (C.c_int, [P, C.POINTER(I)]),
         "sos_residual_noalloc": (C.c_int, [P, P, C.POINTER(D)]),
         "sos_debug_barrier": (C.c_int, [P, C.c_int64, I]),
+        "sos_debug_workspace": (C.c_int, [P, C.c_int64]),
         "sos_optimize_robin": (C.c_int, [I, D, D, I, I, I, D, C.c_uint64, C.POINTER(D), C.POINTER(D),
                                          C.POINTER(I)]),
         "sos_destroy": (None, [P]),
@@ -459,6 +460,11 @@ class Problem:
         """Failure-handling tests: bound of the team barrier's wait (ticks at
         100 MHz, 0 = default) and tag_skew = 1 to make every wait end there."""
         _check(lib().sos_debug_barrier(self.h, int(spin_ticks), int(tag_skew)))
+
+    def debug_workspace(self, limit=0):
+        """Failure-handling tests: bytes above which the on-chip form's workspace
+        counts as a failed allocation (0 = no limit)."""
+        _check(lib().sos_debug_workspace(self.h, int(limit)))
 
     def residual(self, want_phi=True):
         import torch

@@ -660,18 +660,21 @@ size_t fused_res_lds(const sos_ctx* c, int words) {
 }
 
 std::string tune_key(const sos_ctx* c) {
-  // geometry of the subdomain set, precision and inner tolerance
+  // geometry of the subdomain set (the first node's closure index too: it sets
+  // the pairs of a row), precision, inner tolerance, and what selects other
+  // kernels: second-order terms, and whether resident forms may be taken
   uint64_t h = 1469598103934665603ull;
   auto mix = [&](uint64_t v) {
     h ^= v;
     h *= 1099511628211ull;
   };
   for (auto& s : c->subs)
-    for (int a = 0; a < 3; ++a) mix((uint64_t)s.n[a]);
+    for (int a = 0; a < 3; ++a) mix((uint64_t)s.n[a] << 1 | (uint64_t)s.klo[a]);
   mix((uint64_t)c->subs.size());
   char buf[160];
-  snprintf(buf, sizeof buf, "gfx950|v4|%s|%016llx|tol%.3g|abs%.3g|max%d", c->fp32 ? "fp32" : "fp64",
-           (unsigned long long)h, c->opts.inner_tol, c->opts.inner_abs, c->opts.max_inner);
+  snprintf(buf, sizeof buf, "gfx950|v5|%s|%016llx|q%d|res%d|tol%.3g|abs%.3g|max%d", c->fp32 ? "fp32" : "fp64",
+           (unsigned long long)h, c->dev.hasq ? 1 : 0, c->opts.resident, c->opts.inner_tol, c->opts.inner_abs,
+           c->opts.max_inner);
   return buf;
 }
 
@@ -1282,7 +1285,7 @@ constexpr double kTuneMargin = 0.99;
 // lambda = 0), keep the fastest; then, for subdomains of uneven size (more
 // than one size bucket), search each bucket's team size in turn (smallest
 // bucket first, two passes) with the others fixed. The result is cached per (arch,
-// subdomain geometry, precision, inner tolerance).
+// subdomain geometry, precision, inner tolerance, kernel variants: tune_key).
 int autotune(sos_ctx* c) {
   if (c->tuned) {
     // (the on-chip form with another condition may have another plan)
@@ -1299,8 +1302,7 @@ int autotune(sos_ctx* c) {
   if (!partial && tune_lookup(key, &th, &cp, &bt, &ra, &res) && (int)bt.size() == c->n_buckets) {
     ChipPlan plan;
     if (res == 3) {
-      if (std::count(bt.begin(), bt.end(), bt[0]) == (ptrdiff_t)bt.size() && chip_plan(c, bt[0], &plan) &&
-          (!c->opts.team || bt[0] == c->opts.team)) {
+      if (std::count(bt.begin(), bt.end(), bt[0]) == (ptrdiff_t)bt.size() && chip_plan(c, bt[0], &plan)) {
         chip_shape(c, bt[0]);
         if (ensure_fmap(c) == SOS_OK) return SOS_OK;
         if (int rc = chip_leave(c)) return rc;

@@ -89,7 +89,7 @@ int scratch_address(void** out) {
 
 // Launch of the on-chip fused kernel (sos_chip.h).
 struct ChipPlan {
-  int planes = 0, pairs = 0, wl = 0;  // kernel variant
+  int planes = 0, wl = 0;             // kernel variant
   int threads = 0, slots = 0;         // block size, most pairs of a plane
   int team = 0, n_teams = 0;          // blocks per subdomain, teams of the grid
   size_t lds = 0, part = 0, w = 0, x = 0, halo = 0, mail = 0;  // dynamic LDS, workspace bytes
@@ -467,19 +467,9 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   const size_t es = c->fp32 ? 4 : 8;
   ChipPlan p;
   p.team = team;
-  // the kernel variant for 17 pairs a row (16 elements; a row that ends before
-  // its last mid-point has 16 and an idle pair), else any number
-  int most = 0, least = INT32_MAX;
-  for (const SubDesc& d : c->subs) {
-    const int np = chip_pairs(d.n[0], d.klo[0]);
-    most = std::max(most, np);
-    least = std::min(least, np);
-  }
-  p.pairs = most == 17 && least >= 16 ? 17 : 0;
-  auto pairs_of = [&](const SubDesc& d) { return p.pairs ? p.pairs : chip_pairs(d.n[0], d.klo[0]); };
   int waves = 1, zmax = 0;
   for (const SubDesc& d : c->subs) {
-    const int np = pairs_of(d), R = chip_rows(np);
+    const int np = chip_pairs(d.n[0], d.klo[0]), R = chip_rows(np);
     if (R < 1 || (team > 1 && d.n[2] < 2 * team)) return false;
     waves = std::max(waves, (d.n[1] + R - 1) / R);
     zmax = std::max(zmax, (d.n[2] + team - 1) / team);
@@ -490,7 +480,7 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   auto lds_of = [&](bool wl) {
     size_t b = 0;
     for (const SubDesc& d : c->subs)
-      b = std::max(b, chip_lds(pairs_of(d), d.n[1], (d.n[2] + team - 1) / team, es, wl));
+      b = std::max(b, chip_lds(chip_pairs(d.n[0], d.klo[0]), d.n[1], (d.n[2] + team - 1) / team, es, wl));
     return b;
   };
   const size_t limit = c->lds_limit - kChipStatic;
@@ -503,7 +493,6 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   FusedArgs a = {};
   a.team = team;
   a.chip_planes = p.planes;
-  a.chip_pairs = p.pairs;
   a.chip_wl = p.wl;
   a.lds_bytes = (uint32_t)p.lds;
   int dev = 0, cus = 0, per_cu = 0;
@@ -904,7 +893,6 @@ FusedArgs fused_args(sos_ctx* c) {
     a.n_teams = p.n_teams;
     a.nblocks = p.n_teams * p.team;
     a.chip_planes = p.planes;
-    a.chip_pairs = p.pairs;
     a.chip_wl = p.wl;
     a.chip_slots = p.slots;
     a.chip_span = mail_span(a.n_jobs, p.n_teams, c->opts.max_inner);

@@ -230,12 +230,16 @@ __device__ __forceinline__ void chip_sum(double (&v)[N], ChipRed& sh, const Fuse
 
 // ---------------------------------------------------------------------------- kernel
 
-// P: most planes of a block's z-range; NP: pairs per row (0: each subdomain's
-// own number; the offsets of neighbouring rows are then not constants); Q: second-order face terms; WL: w in LDS.
+// P: most planes of a block's z-range; Q: second-order face terms; WL: w in LDS.
+// The number of pairs per row is each subdomain's own. As a compile-time constant (17
+// of them, subdomains 16 elements wide) it puts the offsets of neighbouring rows
+// into the instructions, but up to sixteen more registers spill. Whole solves with and
+// without it: 128^3 in 512 992 against 1011 ms, 96^3 in 216 922 against 914, 48^3 in
+// 27 in FP64 392 against 382, 32 copies of 32^3 133 against 132.
 // From 13 planes on a thread's registers hold r alone: s takes x's place in LDS
 // and x goes to private memory, read and written every second sweep only (two
 // steps along p at once, in the order of the single ones).
-template <typename T, int P, int NP, bool Q, bool WL>
+template <typename T, int P, bool Q, bool WL>
 __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* __restrict__ bfirst, FusedArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ ChipRed sh;
@@ -264,7 +268,7 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
     const int nx = uniform(sd.n[0]), ny = uniform(sd.n[1]), nz = uniform(sd.n[2]);
     const int zb0 = uniform((tau * nz) / TM), zb1 = uniform(((tau + 1) * nz) / TM), zlen = zb1 - zb0;
     const int xk = uniform(sd.klo[0]), yk = uniform(sd.klo[1]), zk = uniform(sd.klo[2]);
-    const int np = NP ? NP : chip_pairs(nx, xk);
+    const int np = chip_pairs(nx, xk);
     const int R = chip_rows(np);
     const int nslots = np * ny;
     const int rq = lane / (np + 1), e = lane - rq * (np + 1);
@@ -286,7 +290,7 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
     int brk = 0, t = 0, epoch = 0, tfail = 0;
     T xstep = T(0);  // step along p that x does not hold yet
     P2<T>* const xg = reinterpret_cast<P2<T>*>(a.chip_x) + (size_t)ticket * (P + kChipAhead) * blockDim.x;
-    if (zmax > P || (TM > 1 && nz < 2 * TM) || chip_pairs(nx, xk) > np || R < 1 ||
+    if (zmax > P || (TM > 1 && nz < 2 * TM) || R < 1 ||
         (ny + R - 1) / R >= (int)(blockDim.x >> 6) || chip_lds(np, ny, zmax, sizeof(T), WL) > a.lds_bytes ||
         nslots > a.chip_slots)
       brk |= kBrkLaunch;  // (the host sizes the launch for every subdomain)

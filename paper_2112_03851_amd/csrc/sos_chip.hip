@@ -9,40 +9,35 @@
 
 namespace sos {
 
-template <typename T, int P, int NP, bool Q, bool WL>
+template <typename T, int P, bool Q, bool WL>
 static hipError_t chip_one(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
                            int* per_cu) {
   if (per_cu)
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void*)k_chip_cg<T, P, NP, Q, WL>, threads,
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void*)k_chip_cg<T, P, Q, WL>, threads,
                                                         a.lds_bytes);
-  hipLaunchKernelGGL((k_chip_cg<T, P, NP, Q, WL>), dim3(a.n_teams * a.team), dim3(threads), a.lds_bytes, st, d,
+  hipLaunchKernelGGL((k_chip_cg<T, P, Q, WL>), dim3(a.n_teams * a.team), dim3(threads), a.lds_bytes, st, d,
                      L.bfirst, a);
   return hipGetLastError();
 }
 
 template <typename T, int P, bool WL>
-static hipError_t chip_np(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
+static hipError_t chip_q(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
                           int* per_cu) {
   if (a.chip_planes != P || (a.chip_wl != 0) != WL) return hipErrorInvalidValue;
-  if (a.chip_pairs == 17)
-    return d.hasq ? chip_one<T, P, 17, true, WL>(d, L, threads, a, st, per_cu)
-                  : chip_one<T, P, 17, false, WL>(d, L, threads, a, st, per_cu);
-  if (a.chip_pairs == 0)
-    return d.hasq ? chip_one<T, P, 0, true, WL>(d, L, threads, a, st, per_cu)
-                  : chip_one<T, P, 0, false, WL>(d, L, threads, a, st, per_cu);
-  return hipErrorInvalidValue;
+  return d.hasq ? chip_one<T, P, true, WL>(d, L, threads, a, st, per_cu)
+                : chip_one<T, P, false, WL>(d, L, threads, a, st, per_cu);
 }
 
 // One set of variants (each set compiled in a translation unit of its own).
 template <int SET>
 hipError_t launch_chip_set(const Dev& d, const SegLaunch& L, int threads, const FusedArgs& a, hipStream_t st,
                            int* per_cu) {
-  if constexpr (SET == 0) return chip_np<float, 17, false>(d, L, threads, a, st, per_cu);
-  else if constexpr (SET == 1) return chip_np<float, 17, true>(d, L, threads, a, st, per_cu);
-  else if constexpr (SET == 2) return chip_np<float, 9, true>(d, L, threads, a, st, per_cu);
-  else if constexpr (SET == 3) return chip_np<float, 5, true>(d, L, threads, a, st, per_cu);
-  else if constexpr (SET == 4) return chip_np<double, 5, true>(d, L, threads, a, st, per_cu);
-  else return chip_np<float, 12, true>(d, L, threads, a, st, per_cu);
+  if constexpr (SET == 0) return chip_q<float, 17, false>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 1) return chip_q<float, 17, true>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 2) return chip_q<float, 9, true>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 3) return chip_q<float, 5, true>(d, L, threads, a, st, per_cu);
+  else if constexpr (SET == 4) return chip_q<double, 5, true>(d, L, threads, a, st, per_cu);
+  else return chip_q<float, 12, true>(d, L, threads, a, st, per_cu);
 }
 
 #define SOS_CHIP_DECL(PREFIX, SET)                                                                      \

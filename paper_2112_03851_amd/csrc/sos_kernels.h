@@ -146,7 +146,7 @@ struct FusedArgs {
   int32_t* queue;                   // [0] block tickets, [1] jobs taken (cleared by the residual kernel), [2] launches since the
                                     // mailboxes were cleared (it counts)
   int32_t n_jobs, n_teams;          // subdomains, teams of the grid
-  int32_t chip_planes, chip_pairs;  // kernel variant: planes per block, pairs per row (0: any)
+  int32_t chip_planes;              // kernel variant: planes per block
   int32_t chip_wl;                  // kernel variant: w in LDS
   int32_t chip_slots;               // most pairs of a plane of any subdomain
   uint32_t chip_span;               // sequence numbers of a launch (sos_mail.h)
@@ -170,7 +170,7 @@ constexpr int kChipPlanes[] = {5, 9, 12, 17};  // most planes per block of the k
 constexpr int kChipAhead = 2;  // planes of w read ahead from the private buffer
 constexpr int kChipPrivate = 5;  // private 4-value records per thread: r, s of four halo planes, the ends' diagonal
 constexpr size_t kChipStatic = 1024;  // room for its static LDS
-// Launches the variant (a.chip_planes, a.chip_pairs, a.chip_wl) on a.n_teams
+// Launches the variant (a.chip_planes, a.chip_wl) on a.n_teams
 // teams; per_cu != NULL: launch nothing, report how many of its blocks a
 // compute unit holds.
 hipError_t launch_chip(const Dev& d, const SegLaunch& L, int fp32, int threads, const FusedArgs& a, hipStream_t st,

@@ -21,6 +21,7 @@
 #include "sos_internal.h"
 #include "sos_kernels.h"
 #include "sos_mail.h"
+#include "sos_tune.h"
 
 using namespace sos;
 
@@ -1263,11 +1264,6 @@ int reset_state(sos_ctx* c) {
   return SOS_OK;
 }
 
-// A candidate replaces the tuner's best only when it is faster by more than
-// the launch-to-launch noise (1 %): the earliest of near-equal shapes wins, so
-// repeated tunings of one problem agree.
-constexpr double kTuneMargin = 0.99;
-
 // Autotuner: time every candidate block shape of the fused kernel with every
 // uniform team size on the first inner solve of the current load (u = 0,
 // lambda = 0), keep the fastest; then, for subdomains of uneven size (more
@@ -1372,8 +1368,7 @@ int autotune(sos_ctx* c) {
   // The on-chip form is kept apart: the others go on to team sizes of their own
   // for each bucket, which may beat it where the uniform ones do not (40
   // subdomains of 16 x 2 x 2 to 8 elements: 0.286 ms on the chip, 0.265 in teams of 8, 2, 2).
-  double best = INFINITY, chip_best = INFINITY;
-  int chip_team = 1;
+  TuneBest best, chip_best;  // (which: the team)
   Shape bs{c->fused_threads, c->fused_cpt, c->fused_ra, c->fused_res};
   std::vector<int32_t> bteams(c->n_buckets, c->fused_team);
   int rc = SOS_OK;
@@ -1394,15 +1389,8 @@ int autotune(sos_ctx* c) {
       double ms = INFINITY;
       if ((rc = time_config(&ms))) break;
       if (cd.res == 3) {
-        // Of near-equal teams the larger one: the trial is a run's longest inner
-        // solve, and in the shorter ones after it the load of r and the update of
-        // u, which take a block a time per plane, weigh more (64^3 elements in 64
-        // subdomains: the trial up to 3 % longer, solves of 677 ms in fours, 701 in
-        // threes).
-        if (ms * 0.97 < chip_best) chip_team = team;
-        chip_best = std::min(chip_best, ms);
-      } else if (ms < best * kTuneMargin) {
-        best = ms;
+        (void)chip_best.offer(team, ms);
+      } else if (best.offer(team, ms)) {
         bs = cd;
         bteams.assign(c->n_buckets, team);
       }
@@ -1410,7 +1398,7 @@ int autotune(sos_ctx* c) {
   // per-bucket team sizes with the best shape: two passes of coordinate
   // descent, smallest bucket first (shrinking the small subdomains' teams
   // frees co-resident blocks that the large ones' teams then need)
-  if (!rc && c->n_buckets > 1 && !c->opts.team && std::isfinite(best) &&
+  if (!rc && c->n_buckets > 1 && !c->opts.team && std::isfinite(best.ms) &&
       fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res) == SOS_OK) {
     for (int pass = 0; pass < 2 * c->n_buckets && !rc; ++pass) {
       const int b = c->n_buckets - 1 - pass % c->n_buckets;
@@ -1422,10 +1410,7 @@ int autotune(sos_ctx* c) {
         if (bs.res && !fused_args(c).res) continue;
         double ms = INFINITY;
         if ((rc = time_config(&ms))) break;
-        if (ms < best * kTuneMargin) {
-          best = ms;
-          bteams = trial;
-        }
+        if (best.offer(t, ms)) bteams = trial;
       }
     }
   }
@@ -1438,11 +1423,11 @@ int autotune(sos_ctx* c) {
   }
   HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (std::isfinite(chip_best) && !(best < chip_best * kTuneMargin)) {
+  if (!tune_replaces(best, chip_best)) {
     best = chip_best;
     bs = {0, 2, 1, 3};
-    bteams.assign(c->n_buckets, chip_team);
-    chip_shape(c, chip_team);
+    bteams.assign(c->n_buckets, chip_best.which);
+    chip_shape(c, chip_best.which);
   } else {
     rc = fused_shape(c, bs.threads, bs.cpt, bs.ra, bs.res);
     if (!rc) rc = set_bucket_teams(c, bteams);
@@ -1451,11 +1436,11 @@ int autotune(sos_ctx* c) {
     c->chip_bytes = 0;
   }
   if (rc) return rc;
-  c->tune_ms = best;
+  c->tune_ms = best.ms;
   invalidate_graph(c);
   // every candidate broke down (a load that is not finite): nothing was learned
-  if (!std::isfinite(best)) c->tuned = false;
-  else if (!partial && !no_memory) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best);
+  if (!std::isfinite(best.ms)) c->tuned = false;
+  else if (!partial && !no_memory) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best.ms);
   return SOS_OK;
 }
 

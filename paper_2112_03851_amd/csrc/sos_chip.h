@@ -577,13 +577,14 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
           const unsigned long long* lo = mail + (size_t)(((tau - 1) * 8 + 4 + 2 * wr + 2 - nlo) * cs + slot) * MW;
           const unsigned long long* hi = mail + (size_t)(((tau + 1) * 8 + 2 * wr) * cs + slot) * MW;
           const size_t up = (size_t)cs * MW;
+          const unsigned want = seq + ((unsigned)a.tag_skew << 31);
           const unsigned long long t0 = wall_clock64();
           for (;;) {
             bool ok = true;
-            if (nlo) ok = mail_read(lo, seq, wlo[0]);
-            if (nlo == 2) ok = mail_read(lo + up, seq, wlo[1]) && ok;
-            if (nhi) ok = mail_read(hi, seq, whi[0]) && ok;
-            if (nhi == 2) ok = mail_read(hi + up, seq, whi[1]) && ok;
+            if (nlo) ok = mail_read(lo, want, wlo[0]);
+            if (nlo == 2) ok = mail_read(lo + up, want, wlo[1]) && ok;
+            if (nhi) ok = mail_read(hi, want, whi[0]) && ok;
+            if (nhi == 2) ok = mail_read(hi + up, want, whi[1]) && ok;
             if (ok) return false;
             if (wall_clock64() - t0 > ticks) return true;
           }

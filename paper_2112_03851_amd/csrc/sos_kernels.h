@@ -151,8 +151,9 @@ struct FusedArgs {
   int32_t chip_slots;               // most pairs of a plane of any subdomain
   uint32_t chip_span;               // sequence numbers of a launch (sos_mail.h)
   void *chip_w, *chip_x, *chip_halo, *chip_mail;  // private w, x, halo r and s, exchanged edge planes
-  int32_t tag_skew;                 // team barrier: 0; 1 waits for a tag no member writes, so
-                                    // every wait ends at spin_ticks (failure-handling tests)
+  int32_t tag_skew;                 // team barrier: 0; 1 waits for a tag (and, on the chip, for mail)
+                                    // that no member writes, so every wait ends at spin_ticks
+                                    // (failure-handling tests)
 };
 // On-chip form of the fused kernel (sos_chip.h). Pairs (a vertex and the
 // mid-point after it) of a row of n nodes whose first has closure index klo;

@@ -60,9 +60,10 @@ struct Seg {
 // address (it is a host-side stand-in there); it uses the device address that
 // hipGetSymbolAddress returns, resolved once per device at set-up.
 constexpr size_t kScratchBytes = size_t(48) << 20;
-// (room beyond the limit for the partials of at most 256 blocks that idle compute
-// units add to a small problem, build_seg: they do not count against it)
-static __device__ __align__(256) unsigned char scratch[kScratchBytes + 8192];
+// (room beyond the limit for the partials of the blocks that idle compute units add
+// to a small problem, build_seg: they do not count against it)
+constexpr int kMaxExtra = 256;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + 2 * kMaxExtra * sizeof(double) + 4096];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -161,6 +162,7 @@ struct sos_ctx {
   bool tuned = false;    // fused block shape chosen (explicit or autotuned)
   double tune_ms = 0.0;  // duration of the chosen shape in the tuning run
   size_t lds_limit = 0;  // LDS of a workgroup, static and dynamic together
+  int units = 256;       // compute units of the device
   // graph of (check_every outer iterations + check)
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
@@ -283,7 +285,7 @@ int build_seg(sos_ctx* c) {
   if ((smax + cpt - 1) / cpt > 1024) return fail(SOS_EINVAL, "x-y plane of %d nodes exceeds the supported maximum", smax);
   int threads = ((smax + cpt - 1) / cpt + 63) / 64 * 64;
   const int n_sub = (int)c->subs.size();
-  const int want = std::max(1, (2 * 256 + n_sub - 1) / n_sub);
+  const int want = std::max(1, (2 * c->units + n_sub - 1) / n_sub);
   // Segments of kMinSeg planes or more pay four extra planes each. Where they
   // leave compute units idle, shorter ones down to two planes, at most one
   // block a compute unit: a march's time is its number of planes then. 16^3
@@ -291,7 +293,7 @@ int build_seg(sos_ctx* c) {
   // form of 32^3 in 8 192 -> 138 ms (32 -> 128 blocks). Not past one block a
   // unit: with 448 blocks for 256 the plain form of 64^3 in 64 subdomains went
   // from 706 to 833 ms, FP32 solves of it from 673 to 704 ms.
-  const int spread = 256 / n_sub;
+  const int spread = std::min(c->units, kMaxExtra) / n_sub;
   g.blocks.clear();
   g.bfirst.assign(1, 0);
   g.extra = 0;
@@ -496,10 +498,8 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   a.chip_planes = p.planes;
   a.chip_wl = p.wl;
   a.lds_bytes = (uint32_t)p.lds;
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      launch_chip(c->dev, c->seg.L, c->fp32, p.threads, a, c->stream, &per_cu) != hipSuccess) {
+  int per_cu = 0;
+  if (launch_chip(c->dev, c->seg.L, c->fp32, p.threads, a, c->stream, &per_cu) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
@@ -508,7 +508,7 @@ bool chip_plan(sos_ctx* c, int team, ChipPlan* out) {
   // which the occupancy query does not see
   const int simd_waves = (p.threads / 64 + 3) / 4;
   per_cu = std::min(per_cu, std::max(1, kChipThreads / 256 / simd_waves));
-  p.n_teams = std::min((int)c->subs.size(), per_cu * cus / team);
+  p.n_teams = std::min((int)c->subs.size(), per_cu * c->units / team);
   if (p.n_teams < 1) return false;
   const size_t blocks = (size_t)p.n_teams * team;
   p.part = align64((int64_t)c->subs.size() * team) * 2 * 4 * sizeof(double);
@@ -1315,7 +1315,7 @@ int autotune(sos_ctx* c) {
     int zmax = 1;
     for (auto& s : c->subs) zmax = std::max(zmax, s.n[2]);
     for (int planes : kChipPlanes) sizes.push_back((zmax + planes - 1) / planes);
-    sizes.push_back(256 / (int)c->subs.size());
+    sizes.push_back(c->units / (int)c->subs.size());
     std::sort(sizes.begin(), sizes.end());
     sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
     for (int t : sizes)
@@ -1671,6 +1671,7 @@ int sos_setup_batch(const sos_mesh* mesh, const sos_partition* part, int32_t cop
     return fail(SOS_ESTATE, "no usable HIP device");
   }
   c->lds_limit = prop.sharedMemPerBlock;
+  c->units = prop.multiProcessorCount;
   if ((rc = scratch_address(&c->scratch))) {
     release(c);
     return rc;

@@ -17,8 +17,11 @@ completes inside the timed region is checked to have reached the tolerance.
 
 Prints one JSON line. The roofline entry comes from the reference solve,
 launched eagerly with HIP events around every fused CG launch on the
-library's stream: algorithmic bytes per launch (12 words per CG iteration and
-local unknown, counted by the kernel) over the average launch duration. The
+library's stream: what bounds the kernel that ran over the average launch
+duration. For the streaming form that is algorithmic bytes (12 words per CG
+iteration and local unknown, counted by the kernel) against HBM; the on-chip
+form keeps those words in registers and LDS, so its entry is FP32 operations
+against the vector units. The
 plain form is timed on a bounded sample of outer iterations. The CPU
 baseline times the oracle (exact subdomain solves) on a bounded sample of the
 same workload.
@@ -39,10 +42,18 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-PMC_GLOB = os.path.join(ROOT, "profiles", "fused_cg_*_pmc.json")
+# FP32 vector peak, which counts packed instructions (two operations a lane); the
+# kernels use none, so half of it is in reach
+VALU_PEAK_TFLOPS = 157.3
+# FP32 operations per node and CG sweep (a fused multiply-add is two), half of those
+# of a vertex and the mid-point after it: y rows 24, x rows 32, z rows 22 on
+# average over vertex and mid-point planes, vector updates and dot products 32
+CHIP_FLOPS_PER_NODE = 55
+PMC_GLOB = os.path.join(ROOT, "profiles", "*_cg_*_pmc.json")
 GOLDEN_COUNTS = os.path.join(ROOT, "tests", "golden", "oracle_outer_counts.json")
 CSRC = os.path.join(ROOT, "paper_2112_03851_amd", "csrc")
-KERNEL_SRCS = [os.path.join(CSRC, n) for n in ("sos_device.h", "sos_kernels.h", "sos_internal.h", "sos_kernels.hip",
+KERNEL_SRCS = [os.path.join(CSRC, n) for n in ("sos_device.h", "sos_kernels.h", "sos_internal.h", "sos_mail.h",
+                                               "sos_kernels.hip",
                                                "sos_fused.hip", "sos_chip.h", "sos_chip.hip")]
 
 
@@ -79,6 +90,37 @@ def measured_traffic(launch_bytes, st, workload_name):
             continue
         return pmc["traffic_over_algorithmic"] * launch_bytes
     return None
+
+
+def roofline_of(st, unknowns, workload_name):
+    """The roofline entry of a solve's fused CG launches, timed by HIP events:
+    the streaming form against HBM, the on-chip form (resident 3) against the
+    vector units. The kernel counts the method's bytes in either form, 48 per local
+    unknown and CG iteration and 20 per local unknown and solve."""
+    launches = st["kernel_launches"]
+    launch_bytes = st["kernel_bytes"] / launches
+    launch_s = st["kernel_ms"] * 1e-3 / launches
+    gbs = launch_bytes / launch_s / 1e9
+    traffic = measured_traffic(launch_bytes, st, workload_name)
+    out = {"traffic": traffic, "avg_launch_ms": launch_s * 1e3, "algorithmic_bytes_per_launch": launch_bytes,
+           "launches": launches, "measured_dram_gbs": traffic / launch_s / 1e9 if traffic else None,
+           "measured_dram_frac": traffic / launch_s / 1e9 / HBM_PEAK_GBS if traffic else None}
+    if st["resident"] != 3:
+        return {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
+                "kernel": "k_fused_cg<float>", **out,
+                "basis": "algorithmic bytes (12 FP32 words per CG iteration and local unknown + the FP64 update "
+                         "of u, counted by the kernel) / average launch duration from HIP events on the "
+                         "library's stream over the eager reference solve"}
+    # one sweep more than CG iterations per inner solve
+    sweeps = (launch_bytes - 20.0 * unknowns) / 48.0 + unknowns
+    tflops = CHIP_FLOPS_PER_NODE * sweeps / launch_s / 1e12
+    return {"bound": "valu", "achieved": tflops, "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "frac": tflops / VALU_PEAK_TFLOPS, "kernel": "k_chip_cg<float>", **out, "method_equivalent_gbs": gbs,
+            "basis": f"{CHIP_FLOPS_PER_NODE} FP32 operations per local unknown and CG sweep (CG iterations + 1 per "
+                     "inner solve) / average launch duration from HIP events on the library's stream over the "
+                     "eager reference solve, against the FP32 vector peak with packed instructions, which are not "
+                     "used; method_equivalent_gbs is the method's 12 words per CG iteration over the same time: "
+                     "words that this form keeps on the chip, no memory traffic"}
 
 
 def log(msg):
@@ -313,24 +355,12 @@ def main():
         raise RuntimeError(f"batched reference solve did not converge: {ref}")
     phi_np = phi.cpu().numpy()
     n_solve = ref["outer_iters"]
-    launch_bytes = ref["kernel_bytes"] / ref["kernel_launches"]
-    launch_s = ref["kernel_ms"] * 1e-3 / ref["kernel_launches"]
-    achieved = launch_bytes / launch_s / 1e9
-    traffic = measured_traffic(launch_bytes, ref, args.workload)
-    roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                "kernel": "k_chip_cg<float>" if ref["resident"] == 3 else "k_fused_cg<float>", "avg_launch_ms": launch_s * 1e3,
-                "algorithmic_bytes_per_launch": launch_bytes, "launches": ref["kernel_launches"],
-                "basis": "algorithmic bytes (12 FP32 words per CG iteration and local unknown + the FP64 update "
-                         "of u, counted by the kernel) / average launch duration from HIP events on the "
-                         "library's stream over the eager reference solve",
-                "measured_dram_gbs": traffic / launch_s / 1e9 if traffic else None,
-                "measured_dram_frac": traffic / launch_s / 1e9 / HBM_PEAK_GBS if traffic else None}
+    lay = prob.layout()
+    roofline = roofline_of(ref, int(np.prod(lay["dims"], axis=1, dtype=np.int64).sum()), args.workload)
 
     # timed steps: graph replays of k outer iterations, solves back to back
     prob.set_opts(timing=0)
     k = every * max(1, -(-n_solve // (args.steps * every)))
-    lay = prob.layout()
     zu = torch.zeros(int(lay["offsets"][-1]), dtype=torch.float64, device="cuda")
     zl = torch.zeros(max(1, int(lay["face_off"][-1])), dtype=torch.float64, device="cuda")
     state = {"pos": 0, "solves": 0, "res": []}

@@ -89,6 +89,15 @@ int scratch_address(void** out) {
 
 }  // namespace
 
+// Block shape of the fused kernel: threads, columns per thread, wave-owned rows,
+// residency.
+struct Shape {
+  int threads, cpt, ra, res;
+  bool operator==(const Shape& o) const {
+    return threads == o.threads && cpt == o.cpt && ra == o.ra && res == o.res;
+  }
+};
+
 // Launch of the on-chip fused kernel (sos_chip.h).
 struct ChipPlan {
   int planes = 0, wl = 0;             // kernel variant
@@ -160,6 +169,7 @@ struct sos_ctx {
   size_t fused_lds = 0;
   double* team_part = nullptr;   // team partial sums
   bool tuned = false;    // fused block shape chosen (explicit or autotuned)
+  Shape stream_shape{0, 0, 0, 0};  // the tuner's best of the streaming form (no threads: unknown)
   double tune_ms = 0.0;  // duration of the chosen shape in the tuning run
   size_t lds_limit = 0;  // LDS of a workgroup, static and dynamic together
   int units = 256;       // compute units of the device
@@ -541,11 +551,14 @@ int chip_reserve(sos_ctx* c, const ChipPlan& p) {
   return SOS_OK;
 }
 
-// Back from the on-chip form to the streaming one as set-up leaves it (the
-// default shape where opts.block does not fit).
+// Back from the on-chip form to the streaming one: the shape that the tuner found
+// best for it, or the one that set-up leaves (the default shape where opts.block does
+// not fit).
 int chip_leave(sos_ctx* c) {
   const sos_opts& o = c->opts;
-  if (fused_shape(c, o.block, 0, o.wave_rows, o.resident) != SOS_OK)
+  const Shape& b = c->stream_shape;
+  if (!(b.threads && !o.block && fused_shape(c, b.threads, b.cpt, b.ra, b.res && o.resident) == SOS_OK) &&
+      fused_shape(c, o.block, 0, o.wave_rows, o.resident) != SOS_OK)
     if (int rc = fused_shape(c, 0, 0, 0, o.resident)) return rc;
   return set_team(c, o.team ? o.team : 1);
 }
@@ -589,13 +602,6 @@ int ensure_fmap(sos_ctx* c) {
   c->fmap_dirty = false;
   return SOS_OK;
 }
-
-struct Shape {
-  int threads, cpt, ra, res;
-  bool operator==(const Shape& o) const {
-    return threads == o.threads && cpt == o.cpt && ra == o.ra && res == o.res;
-  }
-};
 
 // Candidate block shapes of the fused kernel: for 1..4 columns per thread,
 // the smallest block covering the largest plane and 1.5x, 2x, 3x that size
@@ -676,8 +682,10 @@ std::string tune_cache_path() {
 }
 
 // One cached tuning result: "teams" holds one team size per size bucket (an
-// entry with a single "team" is a uniform team, one bucket).
-bool tune_lookup(const std::string& key, int* threads, int* cpt, std::vector<int32_t>* teams, int* ra, int* res) {
+// entry with a single "team" is a uniform team, one bucket); "streaming" the best
+// shape of the streaming form beside an entry of the on-chip form.
+bool tune_lookup(const std::string& key, int* threads, int* cpt, std::vector<int32_t>* teams, int* ra, int* res,
+                 Shape* stream) {
   FILE* f = fopen(tune_cache_path().c_str(), "r");
   if (!f) return false;
   char line[512];
@@ -707,13 +715,19 @@ bool tune_lookup(const std::string& key, int* threads, int* cpt, std::vector<int
     if (w) (void)sscanf(w + 8, "%d", ra);
     const char* v = strstr(line, "\"resident\": ");
     if (v) (void)sscanf(v + 12, "%d", res);
+    const char* b = strstr(line, "\"streaming\": [");
+    Shape s{0, 0, 0, 0};
+    if (!b || sscanf(b + 14, "%d, %d, %d, %d", &s.threads, &s.cpt, &s.ra, &s.res) != 4 || s.threads % 64 ||
+        s.threads < 64 || s.cpt < 1 || s.cpt > 4)
+      s = {0, 0, 0, 0};
+    *stream = s;
   }
   fclose(f);
   return found;
 }
 
 void tune_store(const std::string& key, int threads, int cpt, const std::vector<int32_t>& teams, int ra, int res,
-                double ms) {
+                double ms, const Shape& stream) {
   std::string path = tune_cache_path();
   const size_t slash = path.rfind('/');
   if (slash != std::string::npos) mkdir(path.substr(0, slash).c_str(), 0755);
@@ -723,8 +737,8 @@ void tune_store(const std::string& key, int threads, int cpt, const std::vector<
   for (size_t i = 0; i < teams.size(); ++i) tl += (i ? ", " : "") + std::to_string(teams[i]);
   fprintf(f,
           "{\"key\": \"%s\", \"threads\": %d, \"cpt\": %d, \"teams\": [%s], \"rows\": %d, \"resident\": %d, "
-          "\"ms\": %.4f}\n",
-          key.c_str(), threads, cpt, tl.c_str(), ra, res, ms);
+          "\"ms\": %.4f, \"streaming\": [%d, %d, %d, %d]}\n",
+          key.c_str(), threads, cpt, tl.c_str(), ra, res, ms, stream.threads, stream.cpt, stream.ra, stream.res);
   fclose(f);
 }
 
@@ -1283,7 +1297,7 @@ int autotune(sos_ctx* c) {
   const bool partial = c->opts.block != 0 || c->opts.team != 0;
   int th = 0, cp = 0, ra = 0, res = 0;
   std::vector<int32_t> bt;
-  if (!partial && tune_lookup(key, &th, &cp, &bt, &ra, &res) && (int)bt.size() == c->n_buckets) {
+  if (!partial && tune_lookup(key, &th, &cp, &bt, &ra, &res, &c->stream_shape) && (int)bt.size() == c->n_buckets) {
     ChipPlan plan;
     if (res == 3) {
       if (std::count(bt.begin(), bt.end(), bt[0]) == (ptrdiff_t)bt.size() && chip_plan(c, bt[0], &plan)) {
@@ -1423,6 +1437,7 @@ int autotune(sos_ctx* c) {
   }
   HIPCHK(launch_fill(c->u, c->n_local, 0.0, st));
   HIPCHK(hipStreamSynchronize(st));
+  c->stream_shape = std::isfinite(best.ms) ? bs : Shape{0, 0, 0, 0};
   if (!tune_replaces(best, chip_best)) {
     best = chip_best;
     bs = {0, 2, 1, 3};
@@ -1440,7 +1455,7 @@ int autotune(sos_ctx* c) {
   invalidate_graph(c);
   // every candidate broke down (a load that is not finite): nothing was learned
   if (!std::isfinite(best.ms)) c->tuned = false;
-  else if (!partial && !no_memory) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best.ms);
+  else if (!partial && !no_memory) tune_store(key, bs.threads, bs.cpt, bteams, bs.ra, bs.res, best.ms, c->stream_shape);
   return SOS_OK;
 }
 

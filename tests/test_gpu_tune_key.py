@@ -44,3 +44,29 @@ def test_rows_that_start_elsewhere_are_another_geometry(tmp_path, monkeypatch):
         prob.close()
     keys = [json.loads(v)["key"] for v in cache.read_text().splitlines()]
     assert len(keys) == 2 and keys[0] != keys[1]
+
+
+def test_streaming_shape_stays_known_beside_the_on_chip_form(tmp_path, monkeypatch):
+    """Unequal teams set on a context that the tuner gave the on-chip form run with
+    the tuner's streaming shape, found or read from the cache, as on a context that it
+    gave the streaming form."""
+    import numpy as np
+    import torch
+    from synth.generators import uniform_density
+    cache = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("SOS_TUNE_CACHE", str(cache))
+    case = Case(ne=(48, 48, 48), cuts=((16, 32), (16, 32), (16, 32)), p=16.0)
+    opts = dict(OPTS, precision="fp64", inner_tol=1e-3)
+    d = torch.tensor(uniform_density(case.ne, seed=3), device="cuda")
+    teams = np.where(np.arange(case.part.n_sub) % 2, 1, 2)
+    for k in range(2):  # the search, then its cached entry
+        prob = case.problem(**opts)
+        _, st = prob.solve(d, 1e-6)
+        assert st["resident"] == 3  # (390 against 880 ms a solve)
+        entry = json.loads(cache.read_text())
+        threads, cpt, rows, resident = entry["streaming"]
+        prob.set_teams(teams)
+        _, st = prob.solve(d, 1e-6)
+        assert (st["block"], st["cols_per_thread"], st["wave_rows"], st["team"]) == (threads, cpt, rows, 2), (k, entry)
+        assert st["resident"] != 3 and st["converged"]
+        prob.close()

@@ -19,22 +19,27 @@
 //    halo planes along itself. Blocks are persistent: a team takes subdomains
 //    from the work-ordered list until none is left.
 //
-// What bounds it: the issue of vector instructions (about 90 per pair and
-// plane, three waves per SIMD at 33 x 33 planes) and the latency of a plane's
-// chain, no longer memory. A sweep takes, in cycles of a block at 33 x 33
-// nodes, about 1450 a plane (1830 with every unit busy, 2640 where w is in the
-// private buffer), 2000 to 3000 for each neighbour's two halo planes and 6000 to
-// 9000 for the meeting, most of it two trips between compute units. At 17 x 17
-// nodes in teams of eight a plane takes 980 and a sweep 12000.
+// What bounds it: the latency of a sweep's chain, no longer memory. A sweep is its
+// own planes, one barrier each, whose vector instructions (about 90 per pair and
+// plane, three waves per SIMD at 33 x 33 nodes) are the larger part of them; the
+// neighbours' halo planes, one or two a side; and the meeting, two trips between
+// compute units and the wait for the slowest member. Cycles of one block, from its own
+// clock (profiles/chip_cg_cycles.md): at 33 x 33 nodes 1,460 to 1,550 a plane, 1,940
+// with second-order terms, 2,510 where w is in the private buffer too; 1,700 to 3,100
+// for a neighbour's halo planes; 6,400 to 14,000 for the meeting. So 64^3 elements in
+// 64 subdomains, in fours, spend 11,700 of 29,300 cycles a sweep on their own planes,
+// 128^3 in 512, in threes, 21,300 of 32,700. At 17 x 17 nodes in teams of eight it is
+// 2,900 of 11,900, the meeting 7,000. In FP64 a plane takes 6,200 (registers spill).
 //
-// Whole solves against k_fused_cg, each in its tuned shape: 128^3 elements in
-// 512 subdomains, second-order condition, 1715 -> 980 ms; 96^3 in 216, 1016 ->
-// 914 ms; 64^3 in 64, 772 -> 672 ms; 48^3 in 27, FP64 and adjoint, 878 -> 390 ms.
+// Whole solves against k_fused_cg, each in the shape that the tuner finds best for it,
+// on one box: 128^3 elements in 512 subdomains, second-order condition, 1633 -> 1009
+// ms; 96^3 in 216, 985 -> 914; 64^3 in 64, 701 -> 669; 16^3 in 4, 69.2 -> 64.3; 37 x 29
+// x 23 in 27 uneven, 17.6 -> 17.0; 48^3 in 27, FP64 and adjoint, 767 -> 381.
 // k_fused_cg stays where a plane has few rows and many subdomains fill the chip
 // anyway: a block of six waves leaves no room for a second one on its unit
-// (256 columns of 12 x 12 x 96 nodes: 470 ms there, 690 here; 64 slabs of 11 x 39
-// x 639: 288 against 279 to 330), and where whole subdomains in one block need
-// no team at all (256 of 32^3: 123 against 132 ms).
+// (256 columns of 12 x 12 x 96 nodes: 427 ms there, 694 here; 64 slabs of 11 x 39
+// x 639: 290 against 297), and where whole subdomains in one block need no team at all
+// (256 of 32^3: 123 against 132 ms).
 #pragma once
 
 #include "sos_device.h"

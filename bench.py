@@ -328,8 +328,9 @@ def main():
     drho = torch.tensor(wl.drho(), device="cuda")
     rp, rq, rdesc = robin_of(wl)
     if args.profile_outer:
-        if not (args.block and args.team):
-            raise SystemExit("--profile-outer needs --block and --team (no autotuner launches in a counter run)")
+        if not (args.block and args.team) and not os.path.exists(os.environ.get("SOS_TUNE_CACHE", "")):
+            raise SystemExit("--profile-outer needs --block and --team, or SOS_TUNE_CACHE naming a file that an "
+                             "earlier run filled (no autotuner launches in a counter run)")
         prob = Problem(wl.ne, wl.lengths, wl.bc, cuts=wl.cuts, p=rp, q=rq, G=wl.G, precision="fp32", mode="batched",
                        check_every=args.check_every, inner_tol=args.inner_tol, block=args.block,
                        team=args.team, max_outer=args.profile_outer, timing=1)

@@ -32,7 +32,7 @@
 // 2,900 of 11,900, the meeting 7,000. In FP64 a plane takes 6,200 (registers spill).
 //
 // Whole solves against k_fused_cg, each in the shape that the tuner finds best for it,
-// on one box: 128^3 elements in 512 subdomains, second-order condition, 1633 -> 1009
+// on one GPU: 128^3 elements in 512 subdomains, second-order condition, 1633 -> 1009
 // ms; 96^3 in 216, 985 -> 914; 64^3 in 64, 701 -> 669; 16^3 in 4, 69.2 -> 64.3; 37 x 29
 // x 23 in 27 uneven, 17.6 -> 17.0; 48^3 in 27, FP64 and adjoint, 767 -> 381.
 // k_fused_cg stays where a plane has few rows and many subdomains fill the chip
@@ -777,8 +777,10 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
         if constexpr (sizeof(T) < sizeof(double)) {
           // every step length and direction of the solve descends from the first
           // gamma and delta: FP64 products and sums, as in k_fused_cg (the sums of the
-          // later sweeps are the inner precision's within a thread there too)
-          if (n == 0) {
+          // later sweeps are the inner precision's within a thread there too). Unlikely,
+          // so that the code lies outside the sweeps': amid them it cost 128^3 in 512
+          // (second order) 1004 to 1009 ms a solve, there 995, and without it 991.
+          if (__builtin_expect(n == 0, 0)) {
             g0 = d0 = 0.0;
             uint32_t qw = lds0 + (uint32_t)slot * (uint32_t)sizeof(P2<T>), gw = (uint32_t)tid * (uint32_t)sizeof(P2<T>);
             int k = zb0 + zk, more = zlen;

@@ -777,33 +777,31 @@ __global__ void __launch_bounds__(kChipThreads) k_chip_cg(Dev d, const int32_t* 
         if constexpr (sizeof(T) < sizeof(double)) {
           // every step length and direction of the solve descends from the first
           // gamma and delta: FP64 products and sums, as in k_fused_cg (the sums of the
-          // later sweeps are the inner precision's within a thread there too). Unlikely,
-          // so that the code lies outside the sweeps': amid them it cost 128^3 in 512
-          // (second order) 1004 to 1009 ms a solve, there 995, and without it 991.
+          // later sweeps are the inner precision's within a thread there too), from
+          // the stored p, which is D^-1 r still (forming it again: more code to fetch,
+          // 37 x 29 x 23 elements in 27 17.23 ms a solve, 16.99 so, 16.93 without these
+          // sums). Unlikely, so that the code lies outside the sweeps' (amid them 128^3
+          // in 512, second order, 1004 to 1009 ms, there 996 to 999, without 991).
           if (__builtin_expect(n == 0, 0)) {
             g0 = d0 = 0.0;
             uint32_t qw = lds0 + (uint32_t)slot * (uint32_t)sizeof(P2<T>), gw = (uint32_t)tid * (uint32_t)sizeof(P2<T>);
-            int k = zb0 + zk, more = zlen;
-            asm volatile("" : "+v"(qw), "+v"(gw), "+v"(k), "+v"(more));
-            k = uniform(k);
+            int more = zlen;
+            asm volatile("" : "+v"(qw), "+v"(gw), "+v"(more));
             more = uniform(more);
             unroll<0, P>([&](auto ic) {
               constexpr int i = decltype(ic)::value;
               if (more > 0) {
-                T da, db;
-                dinv(k, da, db);
+                const P2<T> u = lds_at<P2<T>>(px0 + 2 * qw);
                 P2<T> w;
                 if constexpr (WL) w = lds_at<P2<T>>(qw);
                 else w = *reinterpret_cast<const P2<T>*>(reinterpret_cast<const char*>(wg) + gw);
-                const T ua = da * ra[i], ub = db * rb[i];
-                g0 += double(ra[i]) * double(ua);
-                g0 += double(rb[i]) * double(ub);
-                d0 += double(w.a) * double(ua);
-                d0 += double(w.b) * double(ub);
-                if constexpr (WL) qw += plane;
-                else gw += (uint32_t)nthreads * (uint32_t)sizeof(P2<T>);
+                g0 += double(ra[i]) * double(u.a);
+                g0 += double(rb[i]) * double(u.b);
+                d0 += double(w.a) * double(u.a);
+                d0 += double(w.b) * double(u.b);
+                qw += plane;
+                if constexpr (!WL) gw += (uint32_t)nthreads * (uint32_t)sizeof(P2<T>);
                 asm("" : "+v"(qw), "+v"(gw));
-                k = scalar_add<1>(k);
                 more = scalar_add<-1>(more);
               }
             });

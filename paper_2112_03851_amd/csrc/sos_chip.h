@@ -24,7 +24,7 @@
 // plane, three waves per SIMD at 33 x 33 nodes) are the larger part of them; the
 // neighbours' halo planes, one or two a side; and the meeting, two trips between
 // compute units and the wait for the slowest member. Cycles of one block, from its own
-// clock (profiles/chip_cg_cycles.md): at 33 x 33 nodes 1,460 to 1,550 a plane, 1,940
+// clock: at 33 x 33 nodes 1,460 to 1,550 a plane, 1,940
 // with second-order terms, 2,510 where w is in the private buffer too; 1,700 to 3,100
 // for a neighbour's halo planes; 6,400 to 14,000 for the meeting. So 64^3 elements in
 // 64 subdomains, in fours, spend 11,700 of 29,300 cycles a sweep on their own planes,
